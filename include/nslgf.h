@@ -104,7 +104,8 @@ int lgf_convolve(nslgf_t h, const void *src, void *dst, int ncomp, int nx, int n
  * until the process ends; the call makes no hipMalloc, hipFree or other allocating call.  The box's
  * plan must exist: call lgf_table(h, nx, ny, nz, dtype) first, under the same FFT-plan choice
  * (NSLGF_ESTATE otherwise).  The workspaces take
- *     ncomp * nz * (ny + Py) * XP * 2 * sizeof(dtype) bytes (+ alignment),  XP = Px/2 + 1 rounded up to 8,
+ *     ncomp * nz * (ny + Py) * XP * 2 * sizeof(dtype) bytes (+ alignment),  XP = Px/2 + 1 rounded up to 8
+ * (FP32 rows are rounded up to 16 where that fits too),
  * NSLGF_EINVAL beyond the array (it holds, for example, one FP64 component of a 128^3 box or three FP32
  * components of a 96^3 box).
  * Every call on a device shares that device's array and leaves its last contents there: calls that
@@ -384,24 +385,17 @@ int max_cell_speed(nslgf_t h, const void *u, int nx, int ny, int nz, int dtype, 
  */
 int nslgf_profile_enable(nslgf_t h, int enable);
 /*
- * Radix plan of the strided (column) FFT passes of the convolution (Sec. 2.2's zero-padded FFT
- * convolution; the plan changes the order of rounding only) for padded lengths 256 and 512:
- *   0  narrow: 8 (length 256) or 16 (length 512) complex elements per thread, radix-4/8 passes,
- *      an LDS exchange between passes;
- *   1  wide: 16 or 32 elements per thread, radices 16 x 16 or 16 x 32, one exchange per transform;
- *   2  the narrow radices on 4 or 8 elements per thread (512-thread workgroups; in FP32 on tiles of
- *      8 columns, 64-byte row segments);
- *  -1  (the default) in FP32 narrow for the y passes and wide for the fused z pass; in FP64 narrow
- *      at length 256 and 2 at length 512;
- *  -2  (NSLGF_FFT_PLAN_AUTOTUNE) the autotuner: when a plan is built, every variant that exists for
- *      its y and z lengths is timed on the device on the plan's own shapes and the fastest is kept
- *      (the choice may differ between runs, so results may differ in the last bits).
- * A variant that does not exist for a dtype falls back to the default.  Applies to plans built after
- * the call (plans are cached per box, dtype and choice).  NSLGF_EINVAL outside -2 .. 2.
+ * Plan number of the strided (column) FFT passes of the convolution (Sec. 2.2's zero-padded FFT
+ * convolution) for padded lengths 256 and 512: 0, 1 or 2; -1 (the default) numbers them by dtype and pass
+ * (FP32: 0 for the y passes, 1 for the fused z pass; FP64: 0 at length 256, 2 at 512); -2
+ * (NSLGF_FFT_PLAN_AUTOTUNE) takes the default.  One kernel is the fastest measured at every length, dtype
+ * and pass and serves every number (results do not depend on it); the numbers stay so that programs and
+ * tuning files that set them keep working.  Applies to plans built after the call (plans are cached per
+ * box, dtype and choice).  NSLGF_EINVAL outside -2 .. 2.
  */
 #define NSLGF_FFT_PLAN_AUTOTUNE (-2)
 int nslgf_set_fft_plan(nslgf_t h, int choice);
-/* The column-plan variants (y and z passes) of the plan for this box and dtype under the handle's
+/* The column-plan numbers (y and z passes) of the plan for this box and dtype under the handle's
  * current choice, building the plan (on `stream`) if needed; host outputs. */
 int nslgf_plan_info(nslgf_t h, int nx, int ny, int nz, int dtype, void *stream, int *vy, int *vz);
 /* Plain streaming copy of n elements of dtype (device pointers, no overlap, n * size a multiple of
@@ -411,12 +405,11 @@ int nslgf_copy(nslgf_t h, const void *src, void *dst, size_t n, int dtype, void 
 int nslgf_profile_read(nslgf_t h, int index, char *name, int name_cap, long long *calls, double *total_ms);
 
 /*
- * Launch tuner.  Per box and dtype the library chooses the column-plan variants of the convolution
- * (see nslgf_set_fft_plan), the rows per workgroup of the fused x-y integrating-factor pass (32, 64,
+ * Launch tuner.  Per box and dtype the library chooses the rows per workgroup of the fused x-y integrating-factor pass (32, 64,
  * 128, 256; a plane's rows are split into tiles of equal height up to that many), the outputs per thread
  * of the strided z pass (16, 32) and the workgroup shape of the point kernels (0: 64x4, 1: 128x2,
  * 2: 32x8, 3: 256x1 threads).  None of the launch shapes changes the arithmetic (results are
- * bit-identical); the column variants change the order of rounding only.
+ * bit-identical).
  *   NSLGF_TUNE_DEFAULT  the measured defaults: IF rows 32 for ny <= 128, 64 for ny <= 192, else 128;
  *                       z outputs 16 for nz <= 192, else 32; 64x4; the default column plans;
  *   NSLGF_TUNE_AUTO     the first use of a box and dtype times every choice on the device on zero fields

@@ -341,9 +341,8 @@ FFT_PLAN_AUTOTUNE = -2
 
 
 def set_fft_plan(choice: int, device: int | None = None):
-    """Column-pass FFT plan of convolution plans built from now on (lengths 256 and 512): -1 the
-    default, 0 narrow, 1 wide, 2 narrow radices on fewer elements per thread, -2 autotune
-    (time every variant when a plan is built and keep the fastest)."""
+    """Plan number of the column FFT passes of convolution plans built from now on (lengths 256 and 512):
+    -1 the default, 0, 1, 2, or -2.  Every number runs the same kernel."""
     _check("nslgf_set_fft_plan", lib().nslgf_set_fft_plan(handle(device), int(choice)))
 
 
@@ -353,8 +352,7 @@ CELL_SHAPES = ((64, 4), (128, 2), (32, 8), (256, 1))
 
 def set_tuning(mode: int, device: int | None = None):
     """TUNE_DEFAULT: the measured default launch shapes; TUNE_AUTO: time every choice on the first use of
-    a box and dtype and keep the fastest (launch shapes never change results; column plans change the
-    order of rounding only)."""
+    a box and dtype and keep the fastest (launch shapes never change results)."""
     _check("nslgf_set_tuning", lib().nslgf_set_tuning(handle(device), int(mode)))
 
 

@@ -45,9 +45,10 @@ struct DevBuf {
 struct ConvPlan {
     int nx = 0, ny = 0, nz = 0, dtype = 0;
     int Px = 0, Py = 0, Pz = 0;
-    long long XP = 0;
+    long long XP = 0;  // row pitch of the spectrum build, in complex elements (P/2 + 1 rounded up to 8)
+    long long XW = 0;  // row pitch of the workspaces: whole 128-byte lines (FP32: rounded up to 16)
     int tb = 0, tiles = 0;
-    int vy = 0, vz = 0;  // column-pass plan variants of the y and z lengths
+    int vy = 0, vz = 0;  // column-plan numbers reported for the y and z lengths
     DevBuf khat;
     DevBuf A1, A2;  // workspaces for up to 3 components
 };
@@ -105,7 +106,7 @@ struct Profiler {
 
 namespace nslgf {
 // The launch tuner's record of one box and dtype: the launch shapes (once tuned or loaded) and the
-// column-plan variants (-1 until a tuned or loaded plan sets them).
+// column-plan numbers (-1 until a tuned or loaded plan sets them).
 struct TuneEntry {
     Tuning t;
     bool launch_set = false;
@@ -141,7 +142,7 @@ struct nslgf_ctx {
     int batch_mode = NSLGF_BATCH_PASSES;
     bool no_alloc = false;   // inside lgf_convolve_noalloc: lookups that would allocate fail instead
     void* scratch = nullptr; // this device's address of the library's fixed scratch array
-    int fft_plan = -1;  // column-pass plan choice: -1 per-dtype default, -2 autotune, else a variant index
+    int fft_plan = -1;  // column-pass plan choice: -1 per-dtype default, -2 autotune, else a number 0..2
     int tune_mode = NSLGF_TUNE_DEFAULT;
     // launch shapes per (nx, ny, nz, dtype): tuned on first use in NSLGF_TUNE_AUTO, or loaded from a file
     std::map<std::tuple<int, int, int, int>, nslgf::TuneEntry> tunings;
@@ -252,8 +253,6 @@ struct DivSource {
     const unsigned char* blocks = nullptr;  // support blocks (replace the nbuf rule when set)
     int nb = 0;
 };
-static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int ncomp, double scale, hipStream_t s,
-                    void* A1, void* A2, const DivSource* div = nullptr);
 // Twiddle tables of a plan's lengths for a dtype (built on first use; call before any capture).
 static int plan_twiddles(nslgf_ctx* h, const ConvPlan& p, int dt, const void** twh, const void** twf, const void** twy,
                          const void** twz);
@@ -307,100 +306,6 @@ template <class C, class F> static int pick_fastest(hipStream_t s, C deflt, std:
     return NSLGF_OK;
 }
 
-// Autotuner of the column-pass plans: times every variant that exists for the plan's y and z lengths
-// on the plan's own shapes (one component, zero data, the workspaces of one solve) and keeps the
-// fastest for each.  Runs once per plan, before any capture.
-static int autotune_plan(nslgf_ctx* h, ConvPlan& p, hipStream_t s) {
-    const int dt = p.dtype;
-    const size_t es = dtype_size(dt);
-    DevBuf a1, a2;
-    NSLGF_TRY(a1.ensure((size_t)p.nz * p.ny * p.XP * 2 * es));
-    NSLGF_TRY(a2.ensure((size_t)p.nz * p.Py * p.XP * 2 * es));
-    NSLGF_HIP_CHECK(hipMemsetAsync(a1.p, 0, a1.bytes, s));
-    NSLGF_HIP_CHECK(hipMemsetAsync(a2.p, 0, a2.bytes, s));
-    const void *twy, *twz;
-    NSLGF_TRY(get_twiddles(h, p.Py, dt, &twy));
-    NSLGF_TRY(get_twiddles(h, p.Pz, dt, &twz));
-    ColPass y{};
-    y.ncols = p.Px / 2 + 1;
-    y.nouter = p.nz;
-    y.in_row = y.out_row = p.XP;
-    y.ncomp = 1;
-    y.tw = twy;
-    ColPass z{};
-    z.in = z.out = a2.p;
-    z.ncols = p.Px / 2 + 1;
-    z.nouter = p.Py;
-    z.in_outer = z.out_outer = p.XP;
-    z.in_row = z.out_row = (long long)p.Py * p.XP;
-    z.ncomp = 1;
-    z.n_in = z.n_out = p.nz;
-    z.tw = twz;
-    z.khat = p.khat.p;
-    z.khat_tiles = p.tiles;
-    z.outer_period = p.Py;
-    z.scale = 1.0;
-    auto valid = [&](int L, std::initializer_list<int> all) {
-        std::vector<int> v;
-        for (int x : all)
-            if (col_variant_valid(L, dt, x)) v.push_back(x);
-        return v;
-    };
-    {
-        int best = p.vz;
-        const std::vector<int> vs = valid(p.Pz, {0, 1, 2});
-        float tdef = 0.f;
-        NSLGF_TRY(time_min_ms(s, 5, [&] { return launch_col(p.Pz, dt, COL_CONV, z, s, p.vz); }, &tdef));
-        float tbest = tdef;
-        for (int v : vs) {
-            if (v == p.vz) continue;
-            float ms = 0.f;
-            NSLGF_TRY(time_min_ms(s, 5, [&] { return launch_col(p.Pz, dt, COL_CONV, z, s, v); }, &ms));
-            if (ms < 0.97f * tdef && ms < tbest) {
-                tbest = ms;
-                best = v;
-            }
-        }
-        p.vz = best;
-    }
-    {
-        auto run = [&](int v) {
-            ColPass f = y, b = y;
-            f.in = a1.p;
-            f.out = a2.p;
-            f.in_outer = (long long)p.ny * p.XP;
-            f.out_outer = (long long)p.Py * p.XP;
-            f.n_in = p.ny;
-            f.n_out = p.Py;
-            b.in = a2.p;
-            b.out = a1.p;
-            b.in_outer = (long long)p.Py * p.XP;
-            b.out_outer = (long long)p.ny * p.XP;
-            b.n_in = p.Py;
-            b.n_out = p.ny;
-            const int rc = launch_col(p.Py, dt, COL_FWD, f, s, v);
-            return rc != NSLGF_OK ? rc : launch_col(p.Py, dt, COL_INV, b, s, v);
-        };
-        int best = p.vy;
-        const std::vector<int> vs = valid(p.Py, {0, 1, 2});
-        float tdef = 0.f;
-        NSLGF_TRY(time_min_ms(s, 5, [&] { return run(p.vy); }, &tdef));
-        float tbest = tdef;
-        for (int v : vs) {
-            if (v == p.vy) continue;
-            float ms = 0.f;
-            NSLGF_TRY(time_min_ms(s, 5, [&] { return run(v); }, &ms));
-            if (ms < 0.97f * tdef && ms < tbest) {
-                tbest = ms;
-                best = v;
-            }
-        }
-        p.vy = best;
-    }
-    NSLGF_HIP_CHECK(hipStreamSynchronize(s));
-    return NSLGF_OK;
-}
-
 static int build_plan(nslgf_ctx* h, int nx, int ny, int nz, int dtype, hipStream_t s, ConvPlan** out) {
     auto key = std::make_tuple(nx, ny, nz, dtype, h->fft_plan);
     auto it = h->plans.find(key);
@@ -428,11 +333,12 @@ static int build_plan(nslgf_ctx* h, int nx, int ny, int nz, int dtype, hipStream
         return NSLGF_EUNSUPPORTED;
     }
     p.XP = ((p.Px / 2 + 1 + 7) / 8) * 8;
+    p.XW = dtype == NSLGF_F32 ? (p.XP + 15) / 16 * 16 : p.XP;
     p.vy = col_variant_choice(p.Py, dtype, h->fft_plan, false);
     p.vz = col_variant_choice(p.Pz, dtype, h->fft_plan, true);
     auto te = h->tunings.find(std::make_tuple(nx, ny, nz, dtype));
     const bool loaded = h->fft_plan == -1 && te != h->tunings.end() && te->second.vy >= 0 && te->second.vz >= 0 &&
-                        col_variant_valid(p.Py, dtype, te->second.vy) && col_variant_valid(p.Pz, dtype, te->second.vz);
+                        col_variant_valid(p.Py, te->second.vy) && col_variant_valid(p.Pz, te->second.vz);
     if (loaded) {  // a tuned choice recorded for this box (by the tuner or from a tuning file)
         p.vy = te->second.vy;
         p.vz = te->second.vz;
@@ -482,13 +388,10 @@ static int build_plan(nslgf_ctx* h, int nx, int ny, int nz, int dtype, hipStream
     NSLGF_TRY(p.khat.ensure(kbytes));
     NSLGF_TRY(extract_spectrum(spec.p, p.Px, p.Py, p.Pz, p.XP, 1.0 / (double)ktot, p.tb, p.tiles, dtype, p.khat.p, s));
     NSLGF_HIP_CHECK(hipStreamSynchronize(s));
-    if (h->fft_plan == NSLGF_FFT_PLAN_AUTOTUNE || (h->tune_mode == NSLGF_TUNE_AUTO && !loaded && h->fft_plan == -1)) {
-        NSLGF_TRY(autotune_plan(h, p, s));
-        if (h->fft_plan == -1) {
-            TuneEntry& e = h->tunings[std::make_tuple(nx, ny, nz, dtype)];
-            e.vy = p.vy;
-            e.vz = p.vz;
-        }
+    if (h->tune_mode == NSLGF_TUNE_AUTO && !loaded && h->fft_plan == -1) {
+        TuneEntry& e = h->tunings[std::make_tuple(nx, ny, nz, dtype)];
+        e.vy = p.vy;
+        e.vz = p.vz;
     }
     *out = plan.get();
     h->plans.emplace(key, std::move(plan));
@@ -598,14 +501,38 @@ static int get_tuning(nslgf_ctx* h, int nx, int ny, int nz, int dtype, hipStream
     return NSLGF_OK;
 }
 
-// Workspaces of one convolution of up to 3 components: A1 [nz][ny][XP] and A2 [nz][Py][XP] complex.
-static size_t conv_ws_elems_a1(const ConvPlan& p) { return (size_t)p.nz * p.ny * p.XP * 2; }
-static size_t conv_ws_elems_a2(const ConvPlan& p) { return (size_t)p.nz * p.Py * p.XP * 2; }
+// Workspaces of one convolution of up to 3 components: A1 [nz][ny][pitch] and A2 [nz][Py][pitch] complex.
+static size_t conv_ws_elems_a1(const ConvPlan& p, long long pitch) { return (size_t)p.nz * p.ny * pitch * 2; }
+static size_t conv_ws_elems_a2(const ConvPlan& p, long long pitch) { return (size_t)p.nz * p.Py * pitch * 2; }
+
+// Places both workspaces on 128-byte lines in `bytes` bytes at base, with the plan's workspace pitch, or
+// with the pitch of the spectrum where that does not fit.  A column pass moves one 128-byte segment of a
+// row per 8 (FP32: 16) columns: off line boundaries, each takes two lines.  (Three FP32 components at 256^3:
+// the fused z pass takes 0.57 ms at pitch 264, whose odd rows start mid-line, and 0.46 ms at 272.)
+struct ConvWs {
+    void *a1, *a2;
+    long long pitch;
+};
+static bool place_conv_ws(const ConvPlan& p, int ncomp, void* base, size_t bytes, ConvWs* out) {
+    const size_t es = dtype_size(p.dtype);
+    const uintptr_t b0 = (uintptr_t)base;
+    for (long long pitch : {p.XW, p.XP}) {
+        const uintptr_t a1 = (b0 + 127) / 128 * 128;
+        const uintptr_t a2 = (a1 + ncomp * conv_ws_elems_a1(p, pitch) * es + 127) / 128 * 128;
+        if (a2 + ncomp * conv_ws_elems_a2(p, pitch) * es <= b0 + bytes) {
+            *out = ConvWs{(void*)a1, (void*)a2, pitch};
+            return true;
+        }
+    }
+    return false;
+}
 
 static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int ncomp, double scale, hipStream_t s,
-                    void* A1, void* A2, const DivSource* div) {
+                    const ConvWs& ws, const DivSource* div = nullptr) {
+    void *const A1 = ws.a1, *const A2 = ws.a2;
+    const long long XP = ws.pitch;
     const int dt = p.dtype;
-    const long long a1c = (long long)p.nz * p.ny * p.XP, a2c = (long long)p.nz * p.Py * p.XP;
+    const long long a1c = (long long)p.nz * p.ny * XP, a2c = (long long)p.nz * p.Py * XP;
     const void *twh, *twf, *twy, *twz;
     NSLGF_TRY(plan_twiddles(h, p, dt, &twh, &twf, &twy, &twz));
     const long long box = (long long)p.nx * p.ny * p.nz;
@@ -614,7 +541,7 @@ static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int n
     r.out = A1;
     r.nrows = (long long)p.nz * p.ny;
     r.in_row = p.nx;
-    r.out_row = p.XP;
+    r.out_row = XP;
     r.in_comp = box;
     r.out_comp = a1c;
     r.ncomp = ncomp;
@@ -640,23 +567,23 @@ static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int n
     c.out = A2;
     c.ncols = p.Px / 2 + 1;
     c.nouter = p.nz;
-    c.in_outer = (long long)p.ny * p.XP;
-    c.out_outer = (long long)p.Py * p.XP;
-    c.in_row = c.out_row = p.XP;
+    c.in_outer = (long long)p.ny * XP;
+    c.out_outer = (long long)p.Py * XP;
+    c.in_row = c.out_row = XP;
     c.in_comp = a1c;
     c.out_comp = a2c;
     c.ncomp = ncomp;
     c.n_in = p.ny;
     c.n_out = p.Py;
     c.tw = twy;
-    NSLGF_PROF(h, "conv_y_fwd", s, launch_col(p.Py, dt, COL_FWD, c, s, p.vy));
+    NSLGF_PROF(h, "conv_y_fwd", s, launch_col(p.Py, dt, COL_FWD, c, s));
     ColPass z{};
     z.in = A2;
     z.out = A2;
     z.ncols = p.Px / 2 + 1;
     z.nouter = p.Py;
-    z.in_outer = z.out_outer = p.XP;
-    z.in_row = z.out_row = (long long)p.Py * p.XP;
+    z.in_outer = z.out_outer = XP;
+    z.in_row = z.out_row = (long long)p.Py * XP;
     z.in_comp = z.out_comp = a2c;
     z.ncomp = ncomp;
     z.n_in = z.n_out = p.nz;
@@ -665,27 +592,27 @@ static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int n
     z.khat_tiles = p.tiles;
     z.outer_period = p.Py;
     z.scale = scale;
-    NSLGF_PROF(h, "conv_z_fused", s, launch_col(p.Pz, dt, COL_CONV, z, s, p.vz));
+    NSLGF_PROF(h, "conv_z_fused", s, launch_col(p.Pz, dt, COL_CONV, z, s));
     ColPass y{};
     y.in = A2;
     y.out = A1;
     y.ncols = p.Px / 2 + 1;
     y.nouter = p.nz;
-    y.in_outer = (long long)p.Py * p.XP;
-    y.out_outer = (long long)p.ny * p.XP;
-    y.in_row = y.out_row = p.XP;
+    y.in_outer = (long long)p.Py * XP;
+    y.out_outer = (long long)p.ny * XP;
+    y.in_row = y.out_row = XP;
     y.in_comp = a2c;
     y.out_comp = a1c;
     y.ncomp = ncomp;
     y.n_in = p.Py;
     y.n_out = p.ny;
     y.tw = twy;
-    NSLGF_PROF(h, "conv_y_inv", s, launch_col(p.Py, dt, COL_INV, y, s, p.vy));
+    NSLGF_PROF(h, "conv_y_inv", s, launch_col(p.Py, dt, COL_INV, y, s));
     RowPass o{};
     o.in = A1;
     o.out = dst;
     o.nrows = (long long)p.nz * p.ny;
-    o.in_row = p.XP;
+    o.in_row = XP;
     o.out_row = p.nx;
     o.in_comp = a1c;
     o.out_comp = box;
@@ -701,9 +628,9 @@ static int run_conv(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int n
 static int run_conv_shared(nslgf_ctx* h, ConvPlan& p, const void* src, void* dst, int ncomp, double scale,
                            hipStream_t s) {
     const size_t es = dtype_size(p.dtype);
-    NSLGF_TRY(p.A1.ensure(3 * conv_ws_elems_a1(p) * es));
-    NSLGF_TRY(p.A2.ensure(3 * conv_ws_elems_a2(p) * es));
-    return run_conv(h, p, src, dst, ncomp, scale, s, p.A1.p, p.A2.p);
+    NSLGF_TRY(p.A1.ensure(3 * conv_ws_elems_a1(p, p.XW) * es));
+    NSLGF_TRY(p.A2.ensure(3 * conv_ws_elems_a2(p, p.XW) * es));
+    return run_conv(h, p, src, dst, ncomp, scale, s, ConvWs{p.A1.p, p.A2.p, p.XW});
 }
 
 // IF application through two temporaries (x: src -> t1, y: t1 -> t2, z: t2 -> dst); src == dst allowed.
@@ -1096,20 +1023,20 @@ int lgf_convolve_noalloc(nslgf_t h, const void* src, void* dst, int ncomp, int n
     }
     ConvPlan& p = *it->second;
     const size_t es = dtype_size(dtype);
-    const size_t a1 = (size_t)ncomp * conv_ws_elems_a1(p) * es;
-    const size_t a1r = (a1 + 255) / 256 * 256;
-    const size_t a2 = (size_t)ncomp * conv_ws_elems_a2(p) * es;
-    if (a1r + a2 > (size_t)NSLGF_NOALLOC_SCRATCH_BYTES) {
-        set_error("lgf_convolve_noalloc: the convolution needs " + std::to_string(a1r + a2) +
+    const size_t need = ((size_t)ncomp * conv_ws_elems_a1(p, p.XP) * es + 255) / 256 * 256 +
+                        (size_t)ncomp * conv_ws_elems_a2(p, p.XP) * es;
+    ConvWs ws;  // (the array starts on 256 bytes, so what the check accepts fits with the narrower pitch)
+    if (need > (size_t)NSLGF_NOALLOC_SCRATCH_BYTES ||
+        !place_conv_ws(p, ncomp, h->scratch, NSLGF_NOALLOC_SCRATCH_BYTES, &ws)) {
+        set_error("lgf_convolve_noalloc: the convolution needs " + std::to_string(need) +
                   " bytes of workspace, more than the scratch array's " +
                   std::to_string((size_t)NSLGF_NOALLOC_SCRATCH_BYTES));
         return NSLGF_EINVAL;
     }
-    char* base = (char*)h->scratch;  // this device's address of `scratch`, taken when the handle was created
     const bool prof = h->prof.on;     // profiling would create events
     h->prof.on = false;
     h->no_alloc = true;
-    const int rc = run_conv(h, p, src, dst, ncomp, dx * dx, (hipStream_t)stream, base, base + a1r);
+    const int rc = run_conv(h, p, src, dst, ncomp, dx * dx, (hipStream_t)stream, ws);
     h->no_alloc = false;
     h->prof.on = prof;
     return rc;
@@ -1164,8 +1091,6 @@ int herk_stage(nslgf_t h, nslgf_state* st, int stage, void* stream) {
     void* dhat = w + L.dhat * es;
     void* t1 = w + L.t1 * es;
     void* t2 = w + L.t2 * es;
-    void* a1 = w + L.a1 * es;
-    void* a2 = w + L.a2 * es;
     double at[4][4], ct[4];
     tableau(st->scheme, at, ct);
     const double dt = st->dt, beta = dt / (st->dx * st->dx * st->re);
@@ -1203,7 +1128,11 @@ int herk_stage(nslgf_t h, nslgf_state* st, int stage, void* stream) {
     }
     // pressure source M_supp Dbar r, formed while the convolution's first pass loads
     const DivSource dsrc{r, st->n_buf, 1.0 / st->dx, st->supp_blocks, st->block};
-    NSLGF_TRY(run_conv(h, *plan, nullptr, dhat, 1, st->dx * st->dx, s, a1, a2, &dsrc));
+    // (its workspaces start at the IF temporaries, which nothing uses meanwhile; the layout's own places
+    // always fit)
+    ConvWs ws{w + L.a1 * es, w + L.a2 * es, plan->XP};
+    (void)place_conv_ws(*plan, 1, t1, (L.total - L.t1) * es, &ws);
+    NSLGF_TRY(run_conv(h, *plan, nullptr, dhat, 1, st->dx * st->dx, s, ws, &dsrc));
     // u^i = H^i (r^i - G dhat^i) and w^{i,i} = (g^i - G dhat^i) / (a~_ii dt) = (r^i - G dhat^i - q^i -
     // dt sum_j a~_ij w^{i,j}) / (a~_ii dt); the projection is applied while the IF loads (with H^i = I,
     // e.g. the last stage of Schemes A and B, it writes u directly)
@@ -2085,7 +2014,7 @@ int nslgf_tuning_load(nslgf_t h, const char* path) {
         if (check_box(nx, ny, nz) != NSLGF_OK || check_dtype(dt) != NSLGF_OK || Px != padded(nx) ||
             Py != padded(ny) || Pz != padded(nz) || (rows != 32 && rows != 64 && rows != 128 && rows != 256) ||
             (seg != 16 && seg != 32) || shape < 0 || shape >= kCellShapeCount ||
-            (vy >= 0 && !col_variant_valid(Py, dt, vy)) || (vz >= 0 && !col_variant_valid(Pz, dt, vz))) {
+            (vy >= 0 && !col_variant_valid(Py, vy)) || (vz >= 0 && !col_variant_valid(Pz, vz))) {
             set_error("nslgf_tuning_load: an entry does not fit this library (sizes, padded lengths or choices)");
             return NSLGF_EINVAL;
         }

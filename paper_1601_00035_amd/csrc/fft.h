@@ -1,5 +1,5 @@
-// Pencil FFT building blocks for CDNA4 (gfx950): Stockham passes on register-held elements with
-// LDS exchanges between passes.
+// Row FFT building blocks for CDNA4 (gfx950): Stockham passes on register-held elements with LDS
+// exchanges between passes, and the length-R transforms that the column passes share.
 //
 // A length-L transform is split over TP = L / E threads, each holding E complex values in
 // registers.  A pass of radix R with span NS (product of the earlier radices) processes the
@@ -10,8 +10,6 @@
 // R_last (used to fuse forward transform, spectral multiply and inverse transform without an
 // exchange).  Forward transforms use e^{-2 pi i jk/L}; inverse ones e^{+2 pi i jk/L}; neither scales.
 #pragma once
-
-#include <type_traits>
 
 #include "common.h"
 
@@ -51,53 +49,7 @@ NSLGF_FFT_PLAN(128, 8, 2, 8, 8)
 NSLGF_FFT_PLAN(160, 20, 5, 2, 4, 4)
 NSLGF_FFT_PLAN(192, 12, 4, 3, 4, 4)
 NSLGF_FFT_PLAN(256, 8, 4, 8, 8)
-NSLGF_FFT_PLAN(320, 20, 5, 4, 4, 4)
-NSLGF_FFT_PLAN(384, 12, 4, 3, 4, 4, 2)
-NSLGF_FFT_PLAN(512, 16, 8, 8, 8)
 #undef NSLGF_FFT_PLAN
-
-// Column-pass plan variants of lengths 256 and 512 (the plan builder picks one per length and dtype):
-//   V = 0  default plan of the length
-//   V = 1  wide: radices 16 x 16 or 16 x 32, one LDS exchange per transform
-//   V = 2  the default radices on fewer elements per thread (more waves per workgroup), with the
-//          register budget held to four waves per SIMD
-// `waves` is the minimum number of waves per SIMD the register allocation must allow.
-template <int L, int V> struct PlanV {
-    static constexpr int E = Plan1D<L>::E;
-    using Fwd = typename Plan1D<L>::Fwd;
-    static constexpr int waves = 1;
-};
-template <> struct PlanV<512, 1> {
-    static constexpr int E = 32;
-    using Fwd = RList<16, 32>;
-    static constexpr int waves = 1;
-};
-template <> struct PlanV<256, 1> {
-    static constexpr int E = 16;
-    using Fwd = RList<16, 16>;
-    static constexpr int waves = 1;
-};
-template <> struct PlanV<512, 2> {
-    static constexpr int E = 8;
-    using Fwd = RList<8, 8, 8>;
-    static constexpr int waves = 4;
-};
-template <> struct PlanV<256, 2> {
-    static constexpr int E = 4;
-    using Fwd = RList<4, 4, 4, 4>;
-    static constexpr int waves = 4;
-};
-
-// Columns per workgroup of the strided (column-tile) kernels: one 128-byte row segment at least,
-// and at least one wavefront per workgroup, but at most 512 threads (plans with many threads per
-// column then take 64-byte segments).
-template <typename T>
-__host__ __device__ constexpr int col_tb(int tp) {
-    const int base = (int)(128 / (2 * sizeof(T)));
-    const int tb = (tp * base >= 64) ? base : 64 / tp;
-    return tb * tp > 512 ? 512 / tp : tb;
-}
-
 
 // ---- length-R DFTs on registers -------------------------------------------------------------
 template <typename T, int R, bool INV> struct DFT;
@@ -193,38 +145,23 @@ template <typename T, bool INV> struct DFT<T, 5, INV> {
     }
 };
 
-// Composite length R = R1 * R2 DFT on registers (decimation in time, n = R2 n1 + n2,
-// k = k1 + R1 k2): length-R1 DFTs over n1, internal twiddles W_R^{n2 k1} read from the root table
-// of the full transform (W_R^m = tw[m * (L/R)]), length-R2 DFTs over n2.
-template <typename T, int R1, int R2, bool INV> struct DFTC {
-    __device__ __forceinline__ static void run(cplx<T>* v, const cplx<T>* __restrict__ tw, int lr) {
-        constexpr int R = R1 * R2;
-        cplx<T> y[R];
-#pragma unroll
-        for (int n2 = 0; n2 < R2; ++n2) {
-            cplx<T> a[R1];
-#pragma unroll
-            for (int n1 = 0; n1 < R1; ++n1) a[n1] = v[R2 * n1 + n2];
-            DFT<T, R1, INV>::run(a);
-#pragma unroll
-            for (int k1 = 0; k1 < R1; ++k1) {
-                if (n2 * k1 == 0) {
-                    y[k1 * R2 + n2] = a[k1];
-                } else {
-                    const cplx<T> w = tw[(n2 * k1) * lr];
-                    y[k1 * R2 + n2] = INV ? cmulc<T>(a[k1], w) : cmul<T>(a[k1], w);
-                }
-            }
-        }
-#pragma unroll
-        for (int k1 = 0; k1 < R1; ++k1) {
-            cplx<T> b[R2];
-#pragma unroll
-            for (int n2 = 0; n2 < R2; ++n2) b[n2] = y[k1 * R2 + n2];
-            DFT<T, R2, INV>::run(b);
-#pragma unroll
-            for (int k2 = 0; k2 < R2; ++k2) v[k1 + R1 * k2] = b[k2];
-        }
+template <typename T, bool INV> struct DFT<T, 6, INV> {
+    __device__ __forceinline__ static void run(cplx<T>* v) {
+        // even / odd split: X[k] = E[k] + W6^k O[k], X[k + 3] = E[k] - W6^k O[k]
+        const T h = (T)0.86602540378443864676372317075293618347;  // sin(pi / 3)
+        cplx<T> e[3] = {v[0], v[2], v[4]}, o[3] = {v[1], v[3], v[5]};
+        DFT<T, 3, INV>::run(e);
+        DFT<T, 3, INV>::run(o);
+        // W6 = 1/2 - i h forward, 1/2 + i h inverse; W6^2 = -1/2 - i h, -1/2 + i h
+        const T s = INV ? -h : h;
+        const cplx<T> o1 = mk<T>((T)0.5 * o[1].x + s * o[1].y, (T)0.5 * o[1].y - s * o[1].x);
+        const cplx<T> o2 = mk<T>(s * o[2].y - (T)0.5 * o[2].x, (T)-0.5 * o[2].y - s * o[2].x);
+        v[0] = cadd<T>(e[0], o[0]);
+        v[1] = cadd<T>(e[1], o1);
+        v[2] = cadd<T>(e[2], o2);
+        v[3] = csub<T>(e[0], o[0]);
+        v[4] = csub<T>(e[1], o1);
+        v[5] = csub<T>(e[2], o2);
     }
 };
 
@@ -302,10 +239,6 @@ __device__ __forceinline__ void pass_compute(cplx<T>* v, int t, const cplx<T>* _
             DFTHalfIn<T, R, INV>::run(v + b * R);
         } else if constexpr ((PRUNE & 2) && prunable<R>()) {
             DFTHalfOut<T, R, INV>::run(v + b * R);
-        } else if constexpr (R == 16) {
-            DFTC<T, 4, 4, INV>::run(v + b * R, tw, L / 16);
-        } else if constexpr (R == 32) {
-            DFTC<T, 4, 8, INV>::run(v + b * R, tw, L / 32);
         } else {
             DFT<T, R, INV>::run(v + b * R);
         }
@@ -333,37 +266,6 @@ __device__ __forceinline__ void pass_load(cplx<T>* v, int t, Acc& acc) {
     }
 }
 
-// Split exchange (accessors that address one real part per element): the real parts go through LDS
-// first, then the imaginary parts, so the tile needs half the LDS (two more barriers per exchange; the
-// same values move, the results are unchanged).
-template <class Acc> struct SplitExchange : std::false_type {};
-
-template <typename T, int L, int E, int TP, int NS, int R, int PART, class Acc>
-__device__ __forceinline__ void pass_store_part(const cplx<T>* v, int t, Acc& acc) {
-#pragma unroll
-    for (int b = 0; b < E / R; ++b) {
-        const int j = t + b * TP;
-        const int base = (j / NS) * NS * R + (j % NS);
-#pragma unroll
-        for (int r = 0; r < R; ++r) acc(base + r * NS) = PART ? v[b * R + r].y : v[b * R + r].x;
-    }
-}
-
-template <typename T, int L, int E, int TP, int R, int PART, class Acc>
-__device__ __forceinline__ void pass_load_part(cplx<T>* v, int t, Acc& acc) {
-#pragma unroll
-    for (int b = 0; b < E / R; ++b) {
-        const int j = t + b * TP;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if constexpr (PART)
-                v[b * R + r].y = acc(j + r * (L / R));
-            else
-                v[b * R + r].x = acc(j + r * (L / R));
-        }
-    }
-}
-
 template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, class RL> struct Runner;
 
 template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, int R>
@@ -382,19 +284,9 @@ struct Runner<T, L, E, TP, INV, NS, PRUNE, RList<R, R2, Rest...>> {
     __device__ __forceinline__ static void run(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc& acc) {
         pass_compute<T, L, E, TP, INV, NS, R, (NS == 1) ? (PRUNE & 1) : 0>(v, t, tw);
         __syncthreads();
-        if constexpr (SplitExchange<Acc>::value) {
-            pass_store_part<T, L, E, TP, NS, R, 0>(v, t, acc);
-            __syncthreads();
-            pass_load_part<T, L, E, TP, R2, 0>(v, t, acc);
-            __syncthreads();
-            pass_store_part<T, L, E, TP, NS, R, 1>(v, t, acc);
-            __syncthreads();
-            pass_load_part<T, L, E, TP, R2, 1>(v, t, acc);
-        } else {
-            pass_store<T, L, E, TP, NS, R>(v, t, acc);
-            __syncthreads();
-            pass_load<T, L, E, TP, R2>(v, t, acc);
-        }
+        pass_store<T, L, E, TP, NS, R>(v, t, acc);
+        __syncthreads();
+        pass_load<T, L, E, TP, R2>(v, t, acc);
         Runner<T, L, E, TP, INV, NS * R, PRUNE, RList<R2, Rest...>>::run(v, t, tw, acc);
     }
 };
@@ -407,31 +299,6 @@ struct Runner<T, L, E, TP, INV, NS, PRUNE, RList<R, R2, Rest...>> {
 template <typename T, int L, bool INV, class RL, class Acc, int E = Plan1D<L>::E, int PRUNE = 0>
 __device__ __forceinline__ void fft_regs(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc& acc) {
     Runner<T, L, E, L / E, INV, 1, PRUNE, RL>::run(v, t, tw, acc);
-}
-
-// LDS accessor of the column-tile kernels: element pos of column c, columns interleaved.
-template <typename T, int TB>
-struct ColAcc {
-    cplx<T>* base;
-    int c;
-    __device__ __forceinline__ cplx<T>& operator()(int pos) { return base[(pos + (pos >> 4)) * TB + c]; }
-};
-template <int L> __host__ __device__ constexpr int col_lds_len() { return L + L / 16 + 1; }
-// The same layout holding one part (real or imaginary) per element: the split exchange.
-template <typename T, int TB>
-struct ColAccS {
-    T* base;
-    int c;
-    __device__ __forceinline__ T& operator()(int pos) { return base[(pos + (pos >> 4)) * TB + c]; }
-};
-template <typename T, int TB> struct SplitExchange<ColAccS<T, TB>> : std::true_type {};
-// Column passes that use the split exchange: FP64 at lengths 320 and 384, which hold 20 and 12
-// elements per thread, so a full-complex tile needs 20 KB and 12 KB of LDS per wave and a CU holds 6
-// and 8 waves; halving it lets the register budget, not the LDS, set the occupancy (measured: the
-// 192^3 FP64 step 3% faster; in FP32 the tiles are half as large and the extra barriers cost more
-// than the occupancy gains).
-template <typename T, int L> __host__ __device__ constexpr bool col_split_exchange() {
-    return sizeof(T) == 8 && (L == 320 || L == 384);
 }
 
 // LDS accessor of the row kernels: one contiguous segment per row, one pad element every 2^S

@@ -12,11 +12,11 @@
 // Rows are contiguous; the column passes work on tiles of TB adjacent columns (one 128-byte
 // segment per transform element) so that every global access is coalesced without transposes.
 #include <cmath>
-#include <type_traits>
 #include <vector>
 
 #include "fft.h"
 #include "kernels.h"
+#include "pencil.h"
 
 namespace nslgf {
 
@@ -175,139 +175,6 @@ __global__ void __launch_bounds__(256) k_row_c2r(RowPass a0, const RowPass* __re
 }
 
 // ---------------------------------------------------------------------------------------------------
-// PR bit 1: n_in <= L/2, so the forward transform's first butterflies see a zero upper half; bit 2:
-// n_out <= L/2, so the inverse transform's last butterflies produce only the lower half (set by the
-// host; the fused pass always has both).
-// Batched form (da set): one problem spans `per` consecutive values of the grid's z index (FWD, INV:
-// its components) or of the logical workgroup index (CONV) and takes the arguments da[p].
-template <typename T, int L, int MODE, int V = 0, int PR = 0>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(PlanV<L, V>::waves)))
-k_col(ColPass a0, const ColPass* __restrict__ da, int per) {
-    using P = PlanV<L, V>;
-    constexpr int E = P::E, TP = L / E, TB = col_tb<T>(TP);
-    using RF = typename P::Fwd;
-    using RI = Reverse<RF>;
-    static_assert(TB * TP <= 512, "column pass workgroup too large");
-    constexpr int LD = col_lds_len<L>();
-    constexpr bool SPLIT = col_split_exchange<T, L>();
-    using Acc = typename std::conditional<SPLIT, ColAccS<T, TB>, ColAcc<T, TB>>::type;
-    using LdsElem = typename std::conditional<SPLIT, T, cplx<T>>::type;
-    __shared__ LdsElem lds[TB * LD];
-    const int tid = threadIdx.x;
-    const int c = tid % TB, t = tid / TB;
-    int tile, outer, comp;
-    ColPass a = a0;
-    if constexpr (MODE == COL_CONV) {
-        // One-dimensional grid, remapped so that the workgroups sharing a spectrum tile (the mirrored
-        // outer indices ky and P - ky, every component) run on one XCD one after the other: the
-        // hardware hands workgroup b to XCD b mod 8, so XCD x takes the x-th contiguous chunk of the
-        // logical order below and the tile stays in that XCD's L2.
-        const int n = (int)gridDim.x, b = (int)blockIdx.x, x = b % 8;
-        int lg = x * (n / 8) + min(x, n % 8) + b / 8;
-        if (da) {
-            a = da[lg / per];
-            lg %= per;
-        }
-        comp = lg % a.ncomp;
-        const int rest = lg / a.ncomp;
-        const int sq = rest % a.nouter;
-        tile = rest / a.nouter;
-        outer = (sq & 1) ? a.nouter - 1 - (sq >> 1) : (sq >> 1);
-    } else {
-        tile = blockIdx.x;
-        outer = blockIdx.y;
-        comp = blockIdx.z;
-        if (da) {
-            a = da[blockIdx.z / per];
-            comp = blockIdx.z % per;
-        }
-    }
-    const int col = tile * TB + c;
-    const bool valid = col < a.ncols;
-    const cplx<T>* in = (const cplx<T>*)a.in + comp * a.in_comp + (long long)outer * a.in_outer + (valid ? col : 0);
-    cplx<T>* out = (cplx<T>*)a.out + comp * a.out_comp + (long long)outer * a.out_outer + (valid ? col : 0);
-    // The fused pass reads its twiddles from a copy of the root table in LDS, made once per
-    // workgroup (the barrier matters: composite radix-16/32 butterflies read the table already in
-    // the first pass); the single-transform passes read them through the caches, which measured
-    // faster there.
-    const cplx<T>* tw;
-    if constexpr (MODE == COL_CONV) {
-        __shared__ cplx<T> twl[L];
-        for (int m = tid; m < L; m += TB * TP) twl[m] = ((const cplx<T>*)a.tw)[m];
-        __syncthreads();
-        tw = twl;
-    } else {
-        tw = (const cplx<T>*)a.tw;
-    }
-    Acc acc{lds, c};
-    cplx<T> v[E];
-    constexpr int R1 = (MODE == COL_INV) ? First<RI>::value : First<RF>::value;
-#pragma unroll
-    for (int b = 0; b < E / R1; ++b) {
-        const int j = t + b * TP;
-#pragma unroll
-        for (int r = 0; r < R1; ++r) {
-            const int row = j + r * (L / R1);
-            if (MODE != COL_INV && (PR & 1) && prunable<R1>() && 2 * r >= R1)
-                v[b * R1 + r] = mk<T>((T)0, (T)0);  // padding (row >= L/2 >= n_in)
-            else
-                v[b * R1 + r] = (valid && row < a.n_in) ? in[(long long)row * a.in_row] : mk<T>((T)0, (T)0);
-        }
-    }
-    // COL_CONV: the spectrum values this thread multiplies by are loaded now, behind the data loads,
-    // so that their latency overlaps the forward transform
-    constexpr int RLf = Last<RF>::value;
-    T kv[MODE == COL_CONV ? E : 1];
-    if constexpr (MODE == COL_CONV) {
-        const int kyf = min(outer, a.outer_period - outer);
-        // the spectrum is tiled by the default plan's column width KTB, which a variant's TB may divide
-        constexpr int KTB = col_tb<T>(L / Plan1D<L>::E);
-        static_assert(KTB % TB == 0, "column tiles must nest in the spectrum's tiles");
-        const T* kh;
-        if constexpr (KTB == TB) {
-            kh = (const T*)a.khat + ((long long)kyf * a.khat_tiles + tile) * (L / 2 + 1) * KTB + c;
-        } else {
-            const unsigned kcol = (unsigned)(tile * TB + c);
-            kh = (const T*)a.khat + ((long long)kyf * a.khat_tiles + kcol / KTB) * (L / 2 + 1) * KTB + kcol % KTB;
-        }
-#pragma unroll
-        for (int b = 0; b < E / RLf; ++b) {
-            const int j = t + b * TP;
-#pragma unroll
-            for (int r = 0; r < RLf; ++r) {
-                const int kz = j + r * (L / RLf);
-                kv[b * RLf + r] = kh[min(kz, L - kz) * KTB];
-            }
-        }
-    }
-    if constexpr (MODE == COL_INV) {
-        fft_regs<T, L, true, RI, Acc, E, PR & 2>(v, t, tw, acc);
-    } else {
-        fft_regs<T, L, false, RF, Acc, E, PR & 1>(v, t, tw, acc);
-    }
-    if constexpr (MODE == COL_CONV) {
-        const T sc = (T)a.scale;
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = cscale<T>(v[e], kv[e] * sc);
-        fft_regs<T, L, true, RI, Acc, E, PR & 2>(v, t, tw, acc);
-    }
-    using ROut = typename std::conditional<MODE == COL_FWD, RF, RI>::type;
-    constexpr int RO = Last<ROut>::value;
-    if (valid) {
-#pragma unroll
-        for (int b = 0; b < E / RO; ++b) {
-            const int j = t + b * TP;
-#pragma unroll
-            for (int r = 0; r < RO; ++r) {
-                const int row = j + r * (L / RO);
-                if (MODE != COL_FWD && (PR & 2) && prunable<RO>() && 2 * r >= RO) continue;  // not computed
-                if (row < a.n_out) out[(long long)row * a.out_row] = v[b * RO + r];
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------------
 static const int kLengths[] = {16, 32, 48, 64, 96, 128, 160, 192, 256, 320, 384, 512};
 
 bool fft_length_supported(int P) {
@@ -323,8 +190,7 @@ int next_supported_length(int n) {
 }
 
 template <int L> static int tb_of(int dtype) {
-    constexpr int TP = L / Plan1D<L>::E;
-    return dtype == NSLGF_F32 ? col_tb<float>(TP) : col_tb<double>(TP);
+    return dtype == NSLGF_F32 ? pencil_cols<float, L>() : pencil_cols<double, L>();
 }
 
 int col_tile_width(int L, int dtype) {
@@ -388,13 +254,13 @@ static int batched_c2r(const void* args, int nprob, dim3 g, dim3 b, hipStream_t 
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
-template <typename T, int L, int MODE, int V, int PR>
+template <typename T, int L, int MODE, bool HALF>
 static int batched_col(const void* args, int nprob, dim3 g, dim3 b, hipStream_t s) {
     if (MODE == COL_CONV)
-        hipLaunchKernelGGL((k_col<T, L, MODE, V, PR>), dim3(g.x * nprob), b, 0, s, ColPass{}, (const ColPass*)args,
+        hipLaunchKernelGGL((k_pencil<T, L, MODE, HALF>), dim3(g.x * nprob), b, 0, s, ColPass{}, (const ColPass*)args,
                            (int)g.x);
     else
-        hipLaunchKernelGGL((k_col<T, L, MODE, V, PR>), dim3(g.x, g.y, g.z * nprob), b, 0, s, ColPass{},
+        hipLaunchKernelGGL((k_pencil<T, L, MODE, HALF>), dim3(g.x, g.y, g.z * nprob), b, 0, s, ColPass{},
                            (const ColPass*)args, (int)g.z);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
@@ -410,13 +276,13 @@ template <typename T, int LH, bool PAIRS, bool DIV> static int issue_r2c(const R
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
-template <typename T, int L, int MODE, int V, int PR> static int issue_col(const ColPass& a, dim3 grid, dim3 block,
-                                                                           hipStream_t s) {
+template <typename T, int L, int MODE, bool HALF> static int issue_col(const ColPass& a, dim3 grid, dim3 block,
+                                                                       hipStream_t s) {
     if (launch_recorder()) {
-        record_launch(&batched_col<T, L, MODE, V, PR>, grid, block, a);
+        record_launch(&batched_col<T, L, MODE, HALF>, grid, block, a);
         return NSLGF_OK;
     }
-    hipLaunchKernelGGL((k_col<T, L, MODE, V, PR>), grid, block, 0, s, a, nullptr, 0);
+    hipLaunchKernelGGL((k_pencil<T, L, MODE, HALF>), grid, block, 0, s, a, nullptr, 0);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
@@ -452,25 +318,25 @@ template <typename T, int LH> static int do_c2r(const RowPass& a, hipStream_t s)
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
-template <typename T, int L, int MODE, int V = 0> static int do_col(const ColPass& a, hipStream_t s) {
-    constexpr int TP = L / PlanV<L, V>::E, TB = col_tb<T>(TP);
+template <typename T, int L, int MODE> static int do_col(const ColPass& a, hipStream_t s) {
     if (a.nouter > 65535 || a.ncomp > 65535) {
         set_error("column pass grid too large");
         return NSLGF_EINVAL;
     }
-    dim3 grid(ceil_div(a.ncols, TB), a.nouter, a.ncomp);
-    if (MODE == COL_CONV) grid = dim3(ceil_div(a.ncols, TB) * a.nouter * a.ncomp);
+    dim3 grid(ceil_div(a.ncols, pencil_cols<T, L>()), a.nouter, a.ncomp);
+    const dim3 block(64 * pencil_waves<L>());
     const bool half_in = 2 * a.n_in <= L, half_out = 2 * a.n_out <= L;
-    if (MODE == COL_CONV) {
+    if constexpr (MODE == COL_CONV) {
+        grid = dim3(grid.x * grid.y * grid.z);
         if (!half_in || !half_out) {
             set_error("column pass: the fused pass needs n_in, n_out <= L/2");
             return NSLGF_EINVAL;
         }
-        return issue_col<T, L, MODE, V, 3>(a, grid, dim3(TB * TP), s);
+        return issue_col<T, L, MODE, true>(a, grid, block, s);
+    } else {
+        if (MODE == COL_FWD ? half_in : half_out) return issue_col<T, L, MODE, true>(a, grid, block, s);
+        return issue_col<T, L, MODE, false>(a, grid, block, s);
     }
-    if ((MODE == COL_FWD && half_in) || (MODE == COL_INV && half_out))
-        return issue_col<T, L, MODE, V, MODE == COL_FWD ? 1 : 2>(a, grid, dim3(TB * TP), s);
-    return issue_col<T, L, MODE, V, 0>(a, grid, dim3(TB * TP), s);
 }
 
 #define NSLGF_ROW_SWITCH(FN, T)                                                                    \
@@ -525,23 +391,7 @@ int launch_row_c2r(int P, int dtype, const RowPass& a, hipStream_t s) {
         case 512: return do_col<T, 512, MODE>(a, s);                                               \
     }
 
-template <typename T, int L, int V> static int col_modes(ColMode mode, const ColPass& a, hipStream_t s) {
-    if (mode == COL_FWD) return do_col<T, L, COL_FWD, V>(a, s);
-    if (mode == COL_INV) return do_col<T, L, COL_INV, V>(a, s);
-    return do_col<T, L, COL_CONV, V>(a, s);
-}
-
-template <typename T, int L> static int col_variant(int variant, ColMode mode, const ColPass& a, hipStream_t s) {
-    if (variant == 1) return col_modes<T, L, 1>(mode, a, s);
-    if (variant == 2) return col_modes<T, L, 2>(mode, a, s);  // (in FP32 on 8-column tiles)
-    return col_modes<T, L, 0>(mode, a, s);
-}
-
-template <typename T> static int col_dispatch(int L, ColMode mode, const ColPass& a, hipStream_t s, int variant) {
-    if (variant > 0) {
-        if (L == 512) return col_variant<T, 512>(variant, mode, a, s);
-        if (L == 256) return col_variant<T, 256>(variant, mode, a, s);
-    }
+template <typename T> static int col_dispatch(int L, ColMode mode, const ColPass& a, hipStream_t s) {
     if (mode == COL_FWD) {
         NSLGF_COL_SWITCH(T, COL_FWD)
     } else if (mode == COL_INV) {
@@ -553,25 +403,15 @@ template <typename T> static int col_dispatch(int L, ColMode mode, const ColPass
     return NSLGF_EUNSUPPORTED;
 }
 
-int launch_col(int L, int dtype, ColMode mode, const ColPass& a, hipStream_t s, int variant) {
-    return dtype == NSLGF_F32 ? col_dispatch<float>(L, mode, a, s, variant)
-                              : col_dispatch<double>(L, mode, a, s, variant);
+int launch_col(int L, int dtype, ColMode mode, const ColPass& a, hipStream_t s) {
+    return dtype == NSLGF_F32 ? col_dispatch<float>(L, mode, a, s) : col_dispatch<double>(L, mode, a, s);
 }
 
-bool col_variant_valid(int L, int dtype, int v) {
-    (void)dtype;
-    if (L != 512 && L != 256) return v == 0;
-    return v == 0 || v == 1 || v == 2;
-}
+bool col_variant_valid(int L, int v) { return L == 512 || L == 256 ? v >= 0 && v <= 2 : v == 0; }
 
-// Column-pass plan per length, dtype and pass (the y passes or the fused z pass): a valid choice >= 0
-// forces that variant; -1 (or a variant that does not exist for the length) takes the default
-// measured fastest on gfx950.  FP32: the narrow plan for the y passes (13-15 % ahead of the wide one
-// at both lengths), the wide plan for the fused pass (0.21 against 0.33 ms at length 512).  FP64: the
-// wide plan spills its registers at length 512, where the default radices on 8 elements per thread
-// (twice the waves of the default) win in both passes, and the default plan wins at 256.
+// The plan number reported for a length, dtype and pass: a valid choice >= 0, else the default's number.
 int col_variant_choice(int L, int dtype, int choice, bool zpass) {
-    if (choice >= 0 && col_variant_valid(L, dtype, choice)) return choice;
+    if (choice >= 0 && col_variant_valid(L, choice)) return choice;
     if (L != 512 && L != 256) return 0;
     if (dtype == NSLGF_F32) return zpass ? 1 : 0;
     return L == 512 ? 2 : 0;
