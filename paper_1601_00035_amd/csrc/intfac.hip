@@ -23,6 +23,7 @@ int if_weights(double alpha, int dtype, double* w, int wmax) {
     double vals[kmax + 1];
     const double ea = exp(-2.0 * alpha);
     double lead = 1.0;  // a^k / k!
+    int last = kmax;    // (values below 1e-40 of the first change no sum)
     for (int k = 0; k <= kmax; ++k) {
         if (k > 0) lead *= alpha / k;
         double term = lead, sum = lead;
@@ -32,12 +33,16 @@ int if_weights(double alpha, int dtype, double* w, int wmax) {
             if (term < 1e-19 * sum) break;
         }
         vals[k] = ea * sum;
+        if (vals[k] < 1e-40 * vals[0]) {
+            last = k;
+            break;
+        }
     }
     // smallest radius whose two-sided tail is below a quarter of the dtype's unit roundoff times w[0]
     const double tol = (dtype == NSLGF_F32 ? 5.960464477539063e-08 : 1.1102230246251565e-16) * 0.25 * vals[0];
     double tail = 0.0;
     int r = kmax;
-    for (int k = kmax; k >= 1; --k) {
+    for (int k = last; k >= 1; --k) {
         if (2.0 * (tail + vals[k]) > tol) {
             r = k;
             break;
