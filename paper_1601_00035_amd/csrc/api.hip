@@ -787,6 +787,10 @@ static int capture_batched_passes(nslgf_ctx* h, nslgf_state* const* sts, int n, 
     h->capturing = true;  // (no host round trips while recording)
     for (int i = 0; i < n && ok; ++i) {
         const nslgf_state saved = *sts[i];
+        recs[i].alike = (int)std::count_if(sts, sts + n, [&](const nslgf_state* t) {
+            return t->nx == saved.nx && t->ny == saved.ny && t->nz == saved.nz && t->dtype == saved.dtype &&
+                   t->scheme == saved.scheme;
+        });
         launch_recorder() = &recs[i];
         const int rc = ::herk_step(h, sts[i], s);
         launch_recorder() = nullptr;

@@ -144,11 +144,64 @@ struct IfTerms {
     double idx, c_q, c_w1, inv;
 };
 
+// The operands of one input value of the fused x-y passes, and the value formed from them.  Loading and
+// forming are separate so that a pass can have operands under way while it works on earlier rows: a
+// combination or projection formed where it is loaded waits for memory there.
+template <typename T, int MODE> struct IfOperands {
+    static constexpr int N = MODE == IF_IN_PROJ ? 5 : MODE == IF_IN_COMB ? 3 : 1;
+    T v[N];
+};
+template <typename T, int MODE>
+__device__ __forceinline__ void if_load(IfOperands<T, MODE>& o, const T* __restrict__ in, const IfTerms& t, int comp,
+                                        int z, int x, int y, int nx, int ny, int nz, bool inside, bool owned) {
+#pragma unroll
+    for (int i = 0; i < IfOperands<T, MODE>::N; ++i) o.v[i] = (T)0;
+    if (!inside) return;
+    const long long c0 = ((long long)z * ny + y) * nx + x;  // offset within one component
+    const long long e = (long long)comp * nx * ny * nz + c0;
+    o.v[0] = in[e];
+    if constexpr (MODE == IF_IN_COMB) {
+        o.v[1] = ((const T*)t.in1)[e];
+        if (t.in2) o.v[2] = ((const T*)t.in2)[e];
+    } else if constexpr (MODE == IF_IN_PROJ) {
+        const T* D = (const T*)t.dhat;
+        o.v[1] = D[c0];
+        const bool has = comp == 0 ? x + 1 < nx : comp == 1 ? y + 1 < ny : z + 1 < nz;
+        const long long step = comp == 0 ? 1 : comp == 1 ? nx : (long long)nx * ny;
+        if (has) o.v[2] = D[c0 + step];
+        if (t.wnew && owned) {
+            o.v[3] = ((const T*)t.q)[e];
+            if (t.w1) o.v[4] = ((const T*)t.w1)[e];
+        }
+    }
+}
+template <typename T, int MODE>
+__device__ __forceinline__ T if_value(const IfOperands<T, MODE>& o, const IfTerms& t, int comp, int z, int x, int y,
+                                      int nx, int ny, int nz, bool inside, bool owned) {
+    if constexpr (MODE == IF_IN_COMB) {
+        double v = t.c0 * (double)o.v[0];
+        v += t.c1 * (double)o.v[1];
+        if (t.in2) v += t.c2 * (double)o.v[2];
+        return inside ? (T)v : (T)0;
+    } else if constexpr (MODE == IF_IN_PROJ) {
+        const T v = o.v[0] - (o.v[2] - o.v[1]) * (T)t.idx;
+        if (t.wnew && inside && owned) {
+            double base = t.c_q * (double)o.v[3];
+            if (t.w1) base += t.c_w1 * (double)o.v[4];
+            ((T*)t.wnew)[(((long long)comp * nz + z) * ny + y) * nx + x] = (T)(((double)v - base) * t.inv);
+        }
+        return inside ? v : (T)0;
+    } else {
+        return o.v[0];
+    }
+}
+
 // Fused x and y passes (fixed radius R): a workgroup owns one (component, z) plane and S consecutive
 // output rows y0 .. y0 + S - 1 (the tile height, from the rows per workgroup the launch tuner sets per
 // box), one thread per x (nx <= 256).  It walks the rows from y0 - R upwards,
-// RB rows per step: each thread holds the raw values of the next P steps in registers (loads issued
-// P steps ahead), the step's rows go through a double-buffered LDS tile with R zeros at both ends of
+// RB rows per step: each thread holds the operands of the next P steps in registers (loads issued
+// P steps ahead; a projection formed where its operands were loaded waited for memory in every step: FP32
+// 128^3 step 205 -> 151 us in these passes), the step's rows go through a double-buffered LDS tile with R zeros at both ends of
 // each row (one barrier per step), each x-filtered value is rounded to the dtype and pushed into a
 // register window of the last 2R + RB rows, and every row whose 2R + 1 neighbours are in the window
 // is y-filtered and stored.  The values are the ones the separate x and y passes produce (same order
@@ -205,42 +258,18 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
         }
     }
     const int comp = plane / nz, zpl = plane - comp * nz;
-    auto raw = [&](int y) -> T {
-        if (!act || y < 0 || y >= ny) return (T)0;
-        const long long e = pbase + (long long)y * nx + x;
-        if constexpr (MODE == IF_IN_COMB) {
-            double v = terms.c0 * (double)in[e];
-            v += terms.c1 * (double)((const T*)terms.in1)[e];
-            if (terms.in2) v += terms.c2 * (double)((const T*)terms.in2)[e];
-            return (T)v;
-        } else if constexpr (MODE == IF_IN_PROJ) {
-            const T* D = (const T*)terms.dhat;
-            const long long c0 = ((long long)zpl * ny + y) * nx + x;  // offset within one component
-            const T d0 = D[c0];
-            T d1 = (T)0;
-            if (comp == 0) {
-                if (x + 1 < nx) d1 = D[c0 + 1];
-            } else if (comp == 1) {
-                if (y + 1 < ny) d1 = D[c0 + nx];
-            } else {
-                if (zpl + 1 < nz) d1 = D[c0 + (long long)nx * ny];
-            }
-            const T v = in[e] - (d1 - d0) * (T)terms.idx;
-            if (terms.wnew && y >= y0 && y < y0 + S) {
-                double base = terms.c_q * (double)((const T*)terms.q)[e];
-                if (terms.w1) base += terms.c_w1 * (double)((const T*)terms.w1)[e];
-                ((T*)terms.wnew)[e] = (T)(((double)v - base) * terms.inv);
-            }
-            return v;
-        } else {
-            return in[e];
-        }
+    using Ops = IfOperands<T, MODE>;
+    Ops q[P][RB];
+    auto fetch = [&](Ops& o, int y) {
+        if_load<T, MODE>(o, in, terms, comp, zpl, x, y, nx, ny, nz, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
     };
-    T q[P][RB];
+    auto value = [&](const Ops& o, int y) -> T {
+        return if_value<T, MODE>(o, terms, comp, zpl, x, y, nx, ny, nz, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
+    };
 #pragma unroll
     for (int j = 0; j < P; ++j)
 #pragma unroll
-        for (int i = 0; i < RB; ++i) q[j][i] = raw(ylo + j * RB + i);
+        for (int i = 0; i < RB; ++i) fetch(q[j][i], ylo + j * RB + i);
     T win[NW];
 #pragma unroll
     for (int i = 0; i < NW; ++i) win[i] = (T)0;
@@ -248,14 +277,14 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
         T (*lt)[W] = tile_lds[ks & 1];
         if (act) {
 #pragma unroll
-            for (int i = 0; i < RB; ++i) lt[i][R + x] = q[0][i];
+            for (int i = 0; i < RB; ++i) lt[i][R + x] = value(q[0][i], ylo + ks * RB + i);
         }
 #pragma unroll
         for (int j = 0; j < P - 1; ++j)
 #pragma unroll
             for (int i = 0; i < RB; ++i) q[j][i] = q[j + 1][i];
 #pragma unroll
-        for (int i = 0; i < RB; ++i) q[P - 1][i] = raw(ylo + (ks + P) * RB + i);
+        for (int i = 0; i < RB; ++i) fetch(q[P - 1][i], ylo + (ks + P) * RB + i);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 2 * R; ++i) win[i] = win[i + RB];
@@ -281,6 +310,135 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
 #pragma unroll
                 for (int d = 1; d <= R; ++d) acc += wd(d) * (double)(v[R - d] + v[R + d]);
                 out[pbase + (long long)y * nx + x] = (T)acc;
+            }
+        }
+    }
+}
+
+// Fused x and y passes on tiles of at most 64 x 32 outputs of one plane (any nx): the tile and its halo of
+// R points come into LDS at once (independent loads, one memory latency), the x filter runs in place over
+// the rows y0 - R .. y0 + ty + R - 1 (each thread 2 neighbouring outputs from R + 1 pair reads), the y
+// filter reads columns (each thread 8 outputs of one column).  Same operations and roundings as the
+// walking pass below, so the results are equal bit for bit.
+struct IfTileArgs {
+    const void* in;
+    void* out;
+    int nx, ny, nz, ntx, nty, tx, ty;
+    IfWeights wts;
+    IfTerms terms;
+};
+constexpr int kIfTileX = 64, kIfTileY = 32;
+
+template <typename T> struct alignas(2 * sizeof(T)) IfPair {
+    T a, b;
+};
+
+// Batched form (da set): `per` consecutive workgroups make up one problem, whose arguments are da[problem].
+template <typename T, int R, int MODE>
+__global__ void __launch_bounds__(256) k_if_tile(IfTileArgs a0, const IfTileArgs* __restrict__ da, int per) {
+    constexpr int PITCH = kIfTileX + 2 * R + 2;  // (even; two spare elements keep the pair reads of a row inside it)
+    constexpr int ROWS = kIfTileY + 2 * R;
+    __shared__ IfPair<T> lds2[ROWS * PITCH / 2];
+    T* const lds = (T*)lds2;
+    const int nb = (int)gridDim.x, b = (int)blockIdx.x, xcd = b % 8;
+    int lg = xcd * (nb / 8) + min(xcd, nb % 8) + b / 8;
+    const IfTileArgs* A = &a0;
+    if (da) {
+        A = da + lg / per;
+        lg %= per;
+    }
+    const T* __restrict__ in = (const T*)A->in;
+    T* __restrict__ out = (T*)A->out;
+    const int nx = A->nx, ny = A->ny, nz = A->nz, tx = A->tx, ty = A->ty;
+    const IfTerms terms = A->terms;
+    const int itx = lg % A->ntx, ity = (lg / A->ntx) % A->nty, plane = lg / (A->ntx * A->nty);  // plane = comp * nz + z
+    const int comp = plane / nz, z = plane - comp * nz;
+    const int x0 = itx * tx, y0 = ity * ty;
+    const int txe = min(tx, nx - x0), tye = min(ty, ny - y0);  // this tile's outputs (none if the split left it empty)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long pbase = (long long)plane * nx * ny;
+    using Ops = IfOperands<T, MODE>;
+    auto inside = [&](int x, int y) { return x >= 0 && x < nx && y >= 0 && y < ny; };
+    auto owned = [&](int x, int y) { return y >= y0 && y < y0 + tye && x >= x0 && x < x0 + txe; };
+    auto fetch = [&](Ops& o, int x, int y) {
+        if_load<T, MODE>(o, in, terms, comp, z, x, y, nx, ny, nz, inside(x, y), owned(x, y));
+    };
+    auto value = [&](const Ops& o, int x, int y) -> T {
+        return if_value<T, MODE>(o, terms, comp, z, x, y, nx, ny, nz, inside(x, y), owned(x, y));
+    };
+    // rows of the tile and its halo, one row per wave at a time; the columns beyond the first 64 (2R of them
+    // at most) for several rows at once
+    const int nrows = tye + 2 * R, ncols = txe + 2 * R;
+    constexpr int CH = MODE == IF_IN_PROJ ? 4 : 6;  // rows whose loads are in flight together
+    for (int r0 = wave; r0 < nrows; r0 += 4 * CH) {
+        Ops t[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = r0 + 4 * i;
+            fetch(t[i], (r < nrows && lane < ncols) ? x0 - R + lane : -1, y0 - R + r);
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = r0 + 4 * i;
+            if (r < nrows) lds[r * PITCH + lane] = value(t[i], lane < ncols ? x0 - R + lane : -1, y0 - R + r);
+        }
+    }
+    constexpr int HL = 2 * R <= 8 ? 8 : 2 * R <= 16 ? 16 : 32, HR = 256 / HL;  // lanes per row, rows at a time
+    if (ncols > 64) {
+        const int hc = 64 + (int)threadIdx.x % HL;
+        for (int r = (int)threadIdx.x / HL; r < nrows; r += HR) {
+            Ops t;
+            fetch(t, hc < ncols ? x0 - R + hc : -1, y0 - R + r);
+            if (hc < PITCH) lds[r * PITCH + hc] = value(t, hc < ncols ? x0 - R + hc : -1, y0 - R + r);
+        }
+    }
+    __syncthreads();
+    // x filter in place: 32 pairs of outputs per row, 8 rows at a time
+    constexpr int NP = (ROWS + 7) / 8;
+    const int px = ((int)threadIdx.x & 31) * 2, pr = (int)threadIdx.x >> 5;
+    IfPair<T> f[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int r = pr + 8 * i;
+        if (r < nrows && px < txe) {
+            T v[2 * R + 2];
+#pragma unroll
+            for (int k = 0; k <= R; ++k) {
+                const IfPair<T> p = lds2[(r * PITCH + px) / 2 + k];
+                v[2 * k] = p.a;
+                v[2 * k + 1] = p.b;
+            }
+            double s0 = A->wts.w[0] * (double)v[R], s1 = A->wts.w[0] * (double)v[R + 1];
+#pragma unroll
+            for (int d = 1; d <= R; ++d) {
+                s0 += A->wts.w[d] * (double)(v[R - d] + v[R + d]);
+                s1 += A->wts.w[d] * (double)(v[R + 1 - d] + v[R + 1 + d]);
+            }
+            f[i].a = (T)s0;
+            f[i].b = (T)s1;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int r = pr + 8 * i;
+        if (r < nrows && px < txe) lds2[(r * PITCH + px) / 2] = f[i];
+    }
+    __syncthreads();
+    // y filter: wave w takes the output rows 8 w .. 8 w + 7 of every column
+    constexpr int NY = kIfTileY / 4;
+    const int yr = wave * NY;
+    if (lane < txe && yr < tye) {
+        T v[NY + 2 * R];
+#pragma unroll
+        for (int k = 0; k < NY + 2 * R; ++k) v[k] = (yr + k < nrows) ? lds[(yr + k) * PITCH + lane] : (T)0;
+#pragma unroll
+        for (int k = 0; k < NY; ++k) {
+            if (yr + k < tye) {
+                double acc = A->wts.w[0] * (double)v[k + R];
+#pragma unroll
+                for (int d = 1; d <= R; ++d) acc += A->wts.w[d] * (double)(v[k + R - d] + v[k + R + d]);
+                out[pbase + (long long)(y0 + yr + k) * nx + x0 + lane] = (T)acc;
             }
         }
     }
@@ -386,6 +544,27 @@ static void launch_fixed(int axis, const T* in, T* out, int ncomp, int nx, int n
 }
 
 template <typename T, int R, int MODE>
+static int batched_tile(const void* args, int nprob, dim3 g, dim3 b, hipStream_t s) {
+    hipLaunchKernelGGL((k_if_tile<T, R, MODE>), dim3(g.x * nprob), b, 0, s, IfTileArgs{}, (const IfTileArgs*)args,
+                       (int)g.x);
+    NSLGF_LAUNCH_CHECK();
+    return NSLGF_OK;
+}
+template <typename T, int R, int MODE>
+static void issue_tile(const IfXyArgs& x, int ncomp, hipStream_t s) {
+    // tiles of equal size along each axis (none empty: every split has at most one point per tile less than the first)
+    IfTileArgs a{x.in, x.out, x.nx, x.ny, x.nz, ceil_div(x.nx, kIfTileX), ceil_div(x.ny, kIfTileY), 0, 0, x.wts, x.terms};
+    a.tx = ceil_div(x.nx, a.ntx);
+    a.ty = ceil_div(x.ny, a.nty);
+    const dim3 grid((unsigned)((long long)a.ntx * a.nty * a.nz * ncomp)), block(256);
+    if (launch_recorder()) {
+        record_launch(&batched_tile<T, R, MODE>, grid, block, a);
+        return;
+    }
+    hipLaunchKernelGGL((k_if_tile<T, R, MODE>), grid, block, 0, s, a, nullptr, 0);
+}
+
+template <typename T, int R, int MODE>
 static void issue_xy(const IfXyArgs& a, dim3 grid, dim3 block, hipStream_t s) {
     if (launch_recorder()) {
         record_launch(&batched_xy<T, R, MODE>, grid, block, a);
@@ -406,6 +585,12 @@ static void launch_xy(const IfCombine& cb, T* out, int ncomp, int nx, int ny, in
     const dim3 grid((unsigned)((long long)ntiles * nz * ncomp)), block((unsigned)(ceil_div(nx, 64) * 64));
     IfXyArgs a{cb.p[0], out, nx, ny, nz, ntiles, height, wts, IfTerms{}};
     IfTerms& terms = a.terms;
+    // Below two waves per SIMD (2048) the walk's chain of row steps is exposed and the tiles, which load
+    // everything at once, win; above, the walk re-reads fewer halo points (us per plain / projecting launch at
+    // radius 6 or 7, walk against tiles: FP64 48^3 18 / 26 against 11 / 14, 3 components at 96^3 29 against 26,
+    // 6 components at 96^3 37 against 43; FP32 128^3 22 against 23; FP64 256^3 178 against 349).
+    const long long waves = (long long)ntiles * nz * ncomp * ceil_div(nx, 64);
+    const bool tile = waves * (launch_recorder() ? launch_recorder()->alike : 1) < 2048;
     if (cb.proj) {
         const IfProject& pj = *cb.proj;
         terms.dhat = pj.dhat;
@@ -416,16 +601,25 @@ static void launch_xy(const IfCombine& cb, T* out, int ncomp, int nx, int ny, in
         terms.c_q = pj.c_q;
         terms.c_w1 = pj.c_w1;
         terms.inv = pj.inv;
-        issue_xy<T, R, IF_IN_PROJ>(a, grid, block, s);
+        if (tile)
+            issue_tile<T, R, IF_IN_PROJ>(a, ncomp, s);
+        else
+            issue_xy<T, R, IF_IN_PROJ>(a, grid, block, s);
     } else if (cb.p[1]) {
         terms.in1 = cb.p[1];
         terms.in2 = cb.p[2];
         terms.c0 = cb.c[0];
         terms.c1 = cb.c[1];
         terms.c2 = cb.c[2];
-        issue_xy<T, R, IF_IN_COMB>(a, grid, block, s);
+        if (tile)
+            issue_tile<T, R, IF_IN_COMB>(a, ncomp, s);
+        else
+            issue_xy<T, R, IF_IN_COMB>(a, grid, block, s);
     } else {
-        issue_xy<T, R, IF_IN_PLAIN>(a, grid, block, s);
+        if (tile)
+            issue_tile<T, R, IF_IN_PLAIN>(a, ncomp, s);
+        else
+            issue_xy<T, R, IF_IN_PLAIN>(a, grid, block, s);
     }
 }
 

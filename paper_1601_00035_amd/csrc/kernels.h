@@ -24,6 +24,7 @@ struct LaunchRec {
 struct LaunchRecorder {
     std::vector<LaunchRec> recs;
     bool ok = true;  // false once a launch without a batched form was requested
+    int alike = 1;   // problems of the batch with this one's box, dtype and scheme (they share launches)
 };
 LaunchRecorder*& launch_recorder();  // this thread's recorder (null: launch normally)
 template <class A> inline void record_launch(BatchedLaunch fn, dim3 g, dim3 b, const A& a) {
