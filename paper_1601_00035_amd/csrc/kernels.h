@@ -137,7 +137,8 @@ int extract_spectrum(const void* spec, int Px, int Py, int Pz, long long XP, dou
 // Host: w[k] = e^{-2 alpha} I_k(2 alpha), k = 0..r (returns r, the truncation radius for the dtype).
 int if_weights(double alpha, int dtype, double* w, int wmax);
 constexpr int kIfMaxRadius = 63;
-constexpr int kIfFixedMaxRadius = 12;  // radii with compile-time passes (larger ones run the runtime-radius passes)
+constexpr int kIfFixedMaxRadius = 12;  // radii with the fused x-y pass
+constexpr int kIfWideMaxRadius = 24;   // radii with compile-time passes (larger ones run the runtime-radius passes)
 int launch_if_axis(int axis, int dtype, const void* in, void* out, int ncomp, int nx, int ny, int nz,
                    const double* w, int radius, hipStream_t s, int seg = 32);
 // Projection of an IF-HERK stage applied while the fused x-y pass loads (Sec. 3.2, Eq. ifherk_aux_1

@@ -1,6 +1,7 @@
 """The tiled x-y pass of the integrating factor (small launches) at the edges of its tiles: rows of 63, 64,
 65, 128 and 129 points, 31 to 33 and 65 rows, odd widths; against the oracle, and bit for bit against the
-walking pass, which the same fields take when more components fill the chip."""
+walking pass, which the same fields take when more components fill the chip; and the passes of wide radii
+(FP64, 13 to 24 points)."""
 import numpy as np
 import pytest
 import torch
@@ -33,3 +34,14 @@ def test_tile_equals_walk(dtype, ny, nx):
         both = nslgf.if_apply(h, alpha)
         for q in (0, 5):
             assert torch.equal(nslgf.if_apply(h[q:q + 1].contiguous(), alpha)[0], both[q]), (alpha, q)
+
+
+@pytest.mark.parametrize("alpha", [0.25, 0.55, 1.35])
+@pytest.mark.parametrize("shape", [(5, 37, 7), (33, 6, 65), (3, 4, 130)])
+def test_wide_radii_against_oracle(shape, alpha):
+    """Radii of 13 to 24 points (FP64), wider than the box along some axis, odd rows, the ends of the z pass's
+    32-point segments."""
+    h = workloads.random_field((2,) + shape, 11)
+    ref = np.stack([intfac.apply(h[q], alpha) for q in range(2)])
+    out = nslgf.if_apply(torch.from_numpy(h).to(DEV), alpha).cpu().numpy()
+    assert np.abs(out - ref).max() < 1e-13 * np.abs(ref).max()
