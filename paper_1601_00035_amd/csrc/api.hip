@@ -42,6 +42,30 @@ struct DevBuf {
     }
 };
 
+// Pinned host buffer that only grows: kernels write results that the host reads after a synchronisation
+// straight into it (a copy through pageable memory costs a launch and a staging copy more).
+struct HostBuf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    int ensure(size_t need) {
+        if (need <= bytes) return NSLGF_OK;
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 0;
+        if (hipHostMalloc(&p, need, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            set_error("hipHostMalloc of " + std::to_string(need) + " bytes failed");
+            return NSLGF_ENOMEM;
+        }
+        bytes = need;
+        return NSLGF_OK;
+    }
+    ~HostBuf() {
+        if (p) (void)hipHostFree(p);
+    }
+};
+
 struct ConvPlan {
     int nx = 0, ny = 0, nz = 0, dtype = 0;
     int Px = 0, Py = 0, Pz = 0;
@@ -149,6 +173,7 @@ struct nslgf_ctx {
     std::map<std::tuple<int, int, int, int, int>, std::unique_ptr<nslgf::ConvPlan>> plans;
     std::map<std::pair<int, int>, std::unique_ptr<nslgf::DevBuf>> twiddles;  // (L, dtype)
     nslgf::DevBuf if_tmp1, if_tmp2, tmp3, tmp3b, partial, blockmask;
+    nslgf::HostBuf results;  // results that kernels write for the host (every use synchronises before it returns)
     nslgf::DevBuf act_u[2], act_d, act_w, act_work, act_mask;  // the active-box driver's box state
 };
 
@@ -1363,14 +1388,34 @@ static int refresh_into(nslgf_t h, void* u, int nx, int ny, int nz, int n_buf, d
 static int max_abs_host(nslgf_t h, const void* u, int nx, int ny, int nz, int n_buf, int dtype, double* out,
                         hipStream_t s) {
     const int nb = 1024;
-    NSLGF_TRY(h->partial.ensure(nb * sizeof(double)));
-    NSLGF_TRY(launch_max_abs(dtype, u, n_buf, nx, ny, nz, (double*)h->partial.p, nb, s));
-    std::vector<double> host(nb);
-    NSLGF_HIP_CHECK(hipMemcpyAsync(host.data(), h->partial.p, nb * sizeof(double), hipMemcpyDeviceToHost, s));
+    NSLGF_TRY(h->results.ensure(nb * sizeof(double)));
+    const double* host = (const double*)h->results.p;
+    NSLGF_TRY(launch_max_abs(dtype, u, n_buf, nx, ny, nz, (double*)h->results.p, nb, s));
     NSLGF_HIP_CHECK(hipStreamSynchronize(s));
     double m = 0.0;
-    for (double v : host) m = v > m ? v : m;
+    for (int b = 0; b < nb; ++b) m = host[b] > m ? host[b] : m;
     *out = m;
+    return NSLGF_OK;
+}
+
+// Block weights of u into host memory: *mu, *nu point into the handle's result buffer (synchronised; valid
+// until its next use).
+static int block_weights_host(nslgf_t h, int dtype, const void* u, int nx, int ny, int nz, int nb, int n_buf, double dx,
+                              const double** mu, const double** nu, hipStream_t s) {
+    const long long n = (long long)ceil_div(nx, nb) * ceil_div(ny, nb) * ceil_div(nz, nb);
+    NSLGF_TRY(h->results.ensure((size_t)2 * n * sizeof(double)));
+    double* host = (double*)h->results.p;
+    double* d = host;
+    const bool direct = nb <= 16;  // (larger blocks meet in atomics, which need device memory)
+    if (!direct) {
+        NSLGF_TRY(h->partial.ensure((size_t)2 * n * sizeof(double)));
+        d = (double*)h->partial.p;
+    }
+    NSLGF_PROF(h, "block_weights", s, launch_block_weights(dtype, u, nx, ny, nz, nb, n_buf, dx, d, d + n, s));
+    if (!direct) NSLGF_HIP_CHECK(hipMemcpyAsync(host, d, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s));
+    NSLGF_HIP_CHECK(hipStreamSynchronize(s));
+    *mu = host;
+    *nu = host + n;
     return NSLGF_OK;
 }
 
@@ -1471,12 +1516,11 @@ int flow_diagnostics(nslgf_t h, const void* u, int nx, int ny, int nz, int n_buf
     NSLGF_CHECK_ARG(n_buf >= 0, "flow_diagnostics: n_buf must be >= 0");
     NSLGF_CHECK_ARG(std::isfinite(origin[0]) && std::isfinite(origin[1]) && std::isfinite(origin[2]),
                     "flow_diagnostics: origin must be finite");
-    const int nb = 1024;
-    NSLGF_TRY(h->partial.ensure((size_t)nb * kDiagnosticSums * sizeof(double)));
+    const int nb = diagnostics_blocks(nx, ny, nz);
+    NSLGF_TRY(h->results.ensure((size_t)nb * kDiagnosticSums * sizeof(double)));
+    const double* host = (const double*)h->results.p;
     hipStream_t s = (hipStream_t)stream;
-    NSLGF_PROF(h, "diagnostics", s, launch_diagnostics(dtype, u, n_buf, nx, ny, nz, dx, origin, (double*)h->partial.p, nb, s));
-    std::vector<double> host((size_t)nb * kDiagnosticSums);
-    NSLGF_HIP_CHECK(hipMemcpyAsync(host.data(), h->partial.p, host.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    NSLGF_PROF(h, "diagnostics", s, launch_diagnostics(dtype, u, n_buf, nx, ny, nz, dx, origin, (double*)h->results.p, s));
     NSLGF_HIP_CHECK(hipStreamSynchronize(s));
     double sum[kDiagnosticSums] = {};
     for (int b = 0; b < nb; ++b)  // fixed order: the result does not depend on scheduling
@@ -1507,17 +1551,11 @@ int block_weights(nslgf_t h, const void* u, int nx, int ny, int nz, int nb, int 
     NSLGF_CHECK_ARG(n_buf >= 0, "block_weights: n_buf must be >= 0");
     NSLGF_CHECK_ARG(std::isfinite(dx) && dx > 0, "block_weights: dx must be > 0");
     hipStream_t s = (hipStream_t)stream;
-    const long long M = (long long)nx * ny * nz;
-    const long long nblocks = (long long)((nx + nb - 1) / nb) * ((ny + nb - 1) / nb) * ((nz + nb - 1) / nb);
-    NSLGF_TRY(h->tmp3.ensure((size_t)3 * M * dtype_size(dtype)));
-    NSLGF_TRY(h->partial.ensure((size_t)2 * nblocks * sizeof(double)));
-    double* dmu = (double*)h->partial.p;
-    NSLGF_PROF(h, "nonlinear", s, launch_stencil(NSLGF_OP_NONLINEAR, dtype, u, h->tmp3.p, 3, nx, ny, nz, dx, s));
-    NSLGF_PROF(h, "block_weights", s,
-               launch_block_weights(dtype, u, h->tmp3.p, nx, ny, nz, nb, n_buf, dx, dmu, dmu + nblocks, s));
-    NSLGF_HIP_CHECK(hipMemcpyAsync(mu, dmu, nblocks * sizeof(double), hipMemcpyDeviceToHost, s));
-    NSLGF_HIP_CHECK(hipMemcpyAsync(nu, dmu + nblocks, nblocks * sizeof(double), hipMemcpyDeviceToHost, s));
-    NSLGF_HIP_CHECK(hipStreamSynchronize(s));
+    const double *m, *v;
+    NSLGF_TRY(block_weights_host(h, dtype, u, nx, ny, nz, nb, n_buf, dx, &m, &v, s));
+    const size_t bytes = (size_t)ceil_div(nx, nb) * ceil_div(ny, nb) * ceil_div(nz, nb) * sizeof(double);
+    std::memcpy(mu, m, bytes);
+    std::memcpy(nu, v, bytes);
     return NSLGF_OK;
 }
 
@@ -1555,13 +1593,9 @@ int herk_run_adaptive(nslgf_t h, nslgf_state* st, int nsteps, int block, double 
     const int bx = (nx + block - 1) / block, by = (ny + block - 1) / block, bz = (nz + block - 1) / block;
     const long long nbk = (long long)bx * by * bz;
     const long long M = (long long)nx * ny * nz;
-    NSLGF_TRY(h->tmp3.ensure((size_t)3 * M * dtype_size(dt_)));
-    NSLGF_TRY(h->partial.ensure((size_t)2 * nbk * sizeof(double)));
     NSLGF_TRY(h->blockmask.ensure((size_t)2 * nbk));
     unsigned char* dsupp = (unsigned char*)h->blockmask.p;
     unsigned char* dsoln = dsupp + nbk;
-    double* dmu = (double*)h->partial.p;
-    std::vector<double> mu(nbk), nu(nbk);
     std::vector<unsigned char> supp(nbk), soln(nbk), xsoln(nbk), psupp, psoln;
     const StateLayout L = state_layout(nx, ny, nz);
     const size_t es = dtype_size(dt_);
@@ -1582,14 +1616,10 @@ int herk_run_adaptive(nslgf_t h, nslgf_state* st, int nsteps, int block, double 
     } restore{st, st->supp_blocks, st->soln_blocks, st->block};
     for (int step = 0; step < nsteps; ++step) {
         // the domain of this step from the block weights of u (Sec. 4.3)
-        NSLGF_PROF(h, "nonlinear", s, launch_stencil(NSLGF_OP_NONLINEAR, dt_, st->u, h->tmp3.p, 3, nx, ny, nz, st->dx, s));
-        NSLGF_PROF(h, "block_weights", s,
-                   launch_block_weights(dt_, st->u, h->tmp3.p, nx, ny, nz, block, st->n_buf, st->dx, dmu, dmu + nbk, s));
-        NSLGF_HIP_CHECK(hipMemcpyAsync(mu.data(), dmu, nbk * sizeof(double), hipMemcpyDeviceToHost, s));
-        NSLGF_HIP_CHECK(hipMemcpyAsync(nu.data(), dmu + nbk, nbk * sizeof(double), hipMemcpyDeviceToHost, s));
-        NSLGF_HIP_CHECK(hipStreamSynchronize(s));
-        classify_blocks_host(mu.data(), nu.data(), bx, by, bz, eps_supp, eps_soln, n_xb, nullptr, supp.data(),
-                             soln.data(), xsoln.data());
+        const double *mu, *nu;
+        NSLGF_TRY(block_weights_host(h, dt_, st->u, nx, ny, nz, block, st->n_buf, st->dx, &mu, &nu, s));
+        classify_blocks_host(mu, nu, bx, by, bz, eps_supp, eps_soln, n_xb, nullptr, supp.data(), soln.data(),
+                             xsoln.data());
         bool edge = false;
         for (int k = 0; k < bz && !edge; ++k)
             for (int j = 0; j < by && !edge; ++j)
@@ -1663,19 +1693,11 @@ int herk_run_active(nslgf_t h, nslgf_state* st, int nsteps, int block, double ep
         const int bb[3] = {hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2]};
         const long long nbk = (long long)bb[0] * bb[1] * bb[2];
         // classification on the current box (block weights of its velocity, Sec. 4.3)
-        NSLGF_TRY(h->tmp3.ensure((size_t)3 * M * es));
-        NSLGF_TRY(h->partial.ensure((size_t)2 * nbk * sizeof(double)));
-        double* dmu = (double*)h->partial.p;
         void* U = h->act_u[cur].p;
-        NSLGF_PROF(h, "nonlinear", s, launch_stencil(NSLGF_OP_NONLINEAR, dt_, U, h->tmp3.p, 3, bn[0], bn[1], bn[2], st->dx, s));
-        NSLGF_PROF(h, "block_weights", s, launch_block_weights(dt_, U, h->tmp3.p, bn[0], bn[1], bn[2], block, st->n_buf,
-                                                               st->dx, dmu, dmu + nbk, s));
-        std::vector<double> mu(nbk), nu(nbk);
-        NSLGF_HIP_CHECK(hipMemcpyAsync(mu.data(), dmu, nbk * sizeof(double), hipMemcpyDeviceToHost, s));
-        NSLGF_HIP_CHECK(hipMemcpyAsync(nu.data(), dmu + nbk, nbk * sizeof(double), hipMemcpyDeviceToHost, s));
-        NSLGF_HIP_CHECK(hipStreamSynchronize(s));
+        const double *mu, *nu;
+        NSLGF_TRY(block_weights_host(h, dt_, U, bn[0], bn[1], bn[2], block, st->n_buf, st->dx, &mu, &nu, s));
         std::vector<unsigned char> supp(nbk), soln(nbk), xs(nbk);
-        classify_blocks_host(mu.data(), nu.data(), bb[0], bb[1], bb[2], eps_supp, eps_soln, 0, nullptr, supp.data(),
+        classify_blocks_host(mu, nu, bb[0], bb[1], bb[2], eps_supp, eps_soln, 0, nullptr, supp.data(),
                              soln.data(), xs.data());
         // D_supp, D_soln (united with D_supp) in the block coordinates of G, then D_xsoln and its bounding box
         std::fill(gs.begin(), gs.end(), 0);
@@ -1827,14 +1849,13 @@ int max_cell_speed(nslgf_t h, const void* u, int nx, int ny, int nz, int dtype, 
     NSLGF_TRY(check_dtype(dtype));
     NSLGF_CHECK_ARG(u && out, "max_cell_speed: null pointer");
     const int nb = 1024;
-    NSLGF_TRY(h->partial.ensure(nb * sizeof(double)));
+    NSLGF_TRY(h->results.ensure(nb * sizeof(double)));
+    const double* host = (const double*)h->results.p;
     hipStream_t s = (hipStream_t)stream;
-    NSLGF_TRY(launch_max_speed(dtype, u, nx, ny, nz, (double*)h->partial.p, nb, s));
-    std::vector<double> host(nb);
-    NSLGF_HIP_CHECK(hipMemcpyAsync(host.data(), h->partial.p, nb * sizeof(double), hipMemcpyDeviceToHost, s));
+    NSLGF_TRY(launch_max_speed(dtype, u, nx, ny, nz, (double*)h->results.p, nb, s));
     NSLGF_HIP_CHECK(hipStreamSynchronize(s));
     double m = 0.0;
-    for (double v : host) m = v > m ? v : m;
+    for (int b = 0; b < nb; ++b) m = host[b] > m ? host[b] : m;
     *out = m;
     return NSLGF_OK;
 }

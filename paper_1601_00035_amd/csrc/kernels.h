@@ -43,12 +43,18 @@ inline bool recording_unsupported() {
 int enter_handle(nslgf_t h);
 
 // Whether cell (i, j, k) of an nx x ny x nz box lies in the domain: the box shrunk by nbuf cells, or,
-// when blocks is set, the union of the blocks of nb^3 cells marked 1 there (Sec. 4.2; x fastest).
+// when blocks is set, the union of the blocks of nb^3 cells marked 1 there (Sec. 4.2; x fastest).  With
+// M = floor(65536 / nb) + 1, i / nb = (i M) >> 16 for every i < 256 and nb <= 256 (the box limits): one
+// division per thread instead of five per cell (FP64 192^3 with 16^3 blocks: row pass with the divergence
+// 95 -> 89 us, masked curl 64 -> 48 us).
 __device__ __forceinline__ bool in_domain(int i, int j, int k, int nx, int ny, int nz, int nbuf,
                                           const unsigned char* blocks, int nb) {
     if (blocks) {
-        const int bx = (nx + nb - 1) / nb, by = (ny + nb - 1) / nb;
-        return blocks[((k / nb) * by + j / nb) * bx + i / nb] != 0;
+        const unsigned m = 65536u / (unsigned)nb + 1u;
+        const int bx = (int)(((unsigned)(nx - 1) * m) >> 16) + 1, by = (int)(((unsigned)(ny - 1) * m) >> 16) + 1;
+        const int bi = (int)(((unsigned)i * m) >> 16), bj = (int)(((unsigned)j * m) >> 16),
+                  bk = (int)(((unsigned)k * m) >> 16);
+        return blocks[(bk * by + bj) * bx + bi] != 0;
     }
     return i >= nbuf && i < nx - nbuf && j >= nbuf && j < ny - nbuf && k >= nbuf && k < nz - nbuf;
 }
@@ -212,17 +218,18 @@ int launch_copy(const void* in, void* out, size_t bytes, hipStream_t s);
 int launch_masked_curl(int dtype, const void* f, void* e, int nbuf, const unsigned char* blocks, int nb, int nx, int ny,
                        int nz, double dx, hipStream_t s, int shape = 0);
 // per-workgroup maxima of |u^(q)| over the three components on the box shrunk by nbuf points
-int launch_max_abs(int dtype, const void* u, int nbuf, int nx, int ny, int nz, double* dev_partial, int nblocks,
+int launch_max_abs(int dtype, const void* u, int nbuf, int nx, int ny, int nz, double* partial, int nblocks,
                    hipStream_t s);
-// 15 raw sums of the vortex-ring integrals per workgroup into dev_partial[nblocks][15] (order in
+// 15 raw sums of the vortex-ring integrals per workgroup into partial[workgroup][15] (order in
 // stencils.hip), vorticity restricted to the box shrunk by nbuf; origin = coordinates of vertex (0, 0, 0)
 constexpr int kDiagnosticSums = 15;
+int diagnostics_blocks(int nx, int ny, int nz);  // workgroups for a box
 int launch_diagnostics(int dtype, const void* u, int nbuf, int nx, int ny, int nz, double dx, const double origin[3],
-                       double* dev_partial, int nblocks, hipStream_t s);
-// per block of nb^3 cells: mu = max |(C u)^(q)|, nu = max |Dbar nl| (nl = Ntilde(u) on the box), over the
-// points at least nbuf away from every box face; dev_mu, dev_nu hold one value per block (x fastest)
-int launch_block_weights(int dtype, const void* u, const void* nl, int nx, int ny, int nz, int nb, int nbuf, double dx,
-                         double* dev_mu, double* dev_nu, hipStream_t s);
+                       double* partial, hipStream_t s);
+// per block of nb^3 cells: mu = max |(C u)^(q)|, nu = max |Dbar Ntilde(u)| (Ntilde(u) on the box, zero
+// outside), over the points at least nbuf away from every box face; one value per block (x fastest)
+int launch_block_weights(int dtype, const void* u, int nx, int ny, int nz, int nb, int nbuf, double dx, double* mu,
+                         double* nu, hipStream_t s);
 // step guard (guard.hip): acc[0] = max (bits of a nonnegative double) of the FP64 |Dbar u| over the cells at
 // least margin (>= 1) from every face, acc[1] += non-finite values of u (and d when set); reset clears both
 int launch_guard_reset(unsigned long long* acc, hipStream_t s);
@@ -234,7 +241,7 @@ int launch_zero(int dtype, void* dst, long long n, hipStream_t s);
 int launch_copy_box(int dtype, const void* src, const int sdim[3], const int soff[3], void* dst, const int ddim[3],
                     const int doff[3], const int ext[3], int ncomp, hipStream_t s);
 // max over cells of the cell-centred speed
-int launch_max_speed(int dtype, const void* u, int nx, int ny, int nz, double* dev_partial, int nblocks,
+int launch_max_speed(int dtype, const void* u, int nx, int ny, int nz, double* partial, int nblocks,
                      hipStream_t s);
 
 }  // namespace nslgf

@@ -59,8 +59,9 @@ __device__ __forceinline__ T curl_at(const Vec3<T>& f, int q, int i, int j, int 
 // The nine edge values of e = C f it needs (e1, e2, e3 at the cell and one step back along the
 // other axes) use 24 distinct face values, each loaded once: component (1) at offsets
 // (0,0,0), (0,0,+-1), (0,+-1,0), (-1,0,0), (-1,+1,0), (-1,0,+1) and the cyclic images for (2), (3).
+// curl (when given): the three edge values at (i, j, k), as curl_at gives them.
 template <typename T, class V>
-__device__ __forceinline__ void nonlinear_at(const V& f, int i, int j, int k, T idx, T out[3]) {
+__device__ __forceinline__ void nonlinear_at(const V& f, int i, int j, int k, T idx, T out[3], T* curl = nullptr) {
     const auto& F1 = f.c[0];
     const auto& F2 = f.c[1];
     const auto& F3 = f.c[2];
@@ -81,6 +82,11 @@ __device__ __forceinline__ void nonlinear_at(const V& f, int i, int j, int k, T 
     const T e3_0 = (a000 - a0p0 + bp00 - b000) * idx;
     const T e3_jm = (a0m0 - a000 + bpm0 - b0m0) * idx;
     const T e3_im = (am00 - amp0 + b000 - bm00) * idx;
+    if (curl) {
+        curl[0] = e1_0;
+        curl[1] = e2_0;
+        curl[2] = e3_0;
+    }
     out[0] = (T)0.25 * (e2_0 * (c000 + cp00) + e2_km * (c00m + cp0m) - e3_0 * (b000 + bp00) - e3_jm * (b0m0 + bpm0));
     out[1] = (T)0.25 * (e3_0 * (a000 + a0p0) + e3_im * (am00 + amp0) - e1_0 * (c000 + c0p0) - e1_km * (c00m + c0pm));
     out[2] = (T)0.25 * (e1_0 * (b000 + b00p) + e1_jm * (b0m0 + b0mp) - e2_0 * (a000 + a00p) - e2_im * (am00 + am0p));
@@ -331,23 +337,25 @@ int launch_copy(const void* in, void* out, size_t bytes, hipStream_t s) {
     return NSLGF_OK;
 }
 
+// Largest cell-centred speed per workgroup; a wave walks whole rows (one index division per row), and the
+// square root, monotone, is taken once of the largest square.
 template <typename T>
 __global__ void __launch_bounds__(256) k_max_speed(const T* u, int nx, int ny, int nz, double* partial) {
-    const long long n = (long long)nx * ny * nz;
+    const long long n = (long long)nx * ny * nz, sxy = (long long)nx * ny;
     __shared__ double red[256];
     double m = 0.0;
-    for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < n;
-         idx += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(idx % nx);
-        const int j = (int)((idx / nx) % ny);
-        const int k = (int)(idx / ((long long)nx * ny));
-        Vec3<T> U = vec3(u, nx, ny, nz);
-        const double a = 0.5 * ((double)U.c[0](i, j, k) + (double)U.c[0](i - 1, j, k));
-        const double b = 0.5 * ((double)U.c[1](i, j, k) + (double)U.c[1](i, j - 1, k));
-        const double c = 0.5 * ((double)U.c[2](i, j, k) + (double)U.c[2](i, j, k - 1));
-        m = fmax(m, sqrt(a * a + b * b + c * c));
+    const int nrows = ny * nz;
+    for (int row = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6); row < nrows; row += (int)gridDim.x * 4) {
+        const int k = row / ny, j = row - k * ny;
+        const T* p = u + (long long)row * nx;
+        for (int i = (int)threadIdx.x & 63; i < nx; i += 64) {
+            const double a = 0.5 * ((double)p[i] + (double)(i > 0 ? p[i - 1] : (T)0));
+            const double b = 0.5 * ((double)p[n + i] + (double)(j > 0 ? p[n + i - nx] : (T)0));
+            const double c = 0.5 * ((double)p[2 * n + i] + (double)(k > 0 ? p[2 * n + i - sxy] : (T)0));
+            m = fmax(m, a * a + b * b + c * c);
+        }
     }
-    red[threadIdx.x] = m;
+    red[threadIdx.x] = sqrt(m);
     __syncthreads();
     for (int s = blockDim.x / 2; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
@@ -393,107 +401,174 @@ __global__ void __launch_bounds__(256) k_max_abs(const T* u, int nx, int ny, int
 // each vorticity component (edge (q) is half a cell back along axis q); K and J average u (two faces)
 // and w (four edges) to the cell centres.  Point (i, j, k) with offsets -1/2 on the flagged axes sits
 // at origin + (i, j, k) dx - dx/2 on those axes.
-template <typename T>
-__device__ __forceinline__ double edge_w(const Vec3<T>& U, int q, int i, int j, int k, int nx, int ny, int nz, T idx,
-                                         int nbuf) {
-    if (i < nbuf || j < nbuf || k < nbuf || i >= nx - nbuf || j >= ny - nbuf || k >= nz - nbuf) return 0.0;
-    return (double)curl_at(U, q, i, j, k, idx);
+// A workgroup takes a tile of 31 x 15 cells (32 x 16 threads: one more column and row below, whose edge
+// values the averages need) and walks up to kDiagZ planes: every edge vorticity is formed once per tile,
+// neighbours in the plane come through LDS and those of the plane below stay in registers.  (One thread per
+// cell that formed its twelve edge values itself took 235 us at 192^3 in FP64, bound by instructions; this
+// one 93.)
+constexpr int kDiagX = 32, kDiagY = 16, kDiagZ = 24;
+static dim3 diag_grid(int nx, int ny, int nz) {
+    return dim3(ceil_div(nx, kDiagX - 1), ceil_div(ny, kDiagY - 1), ceil_div(nz, kDiagZ));
 }
-
+int diagnostics_blocks(int nx, int ny, int nz) {
+    const dim3 g = diag_grid(nx, ny, nz);
+    return (int)(g.x * g.y * g.z);
+}
 template <typename T>
-__global__ void __launch_bounds__(256) k_diagnostics(const T* u, int nx, int ny, int nz, int nbuf, T idx, double dx,
-                                                     double ox, double oy, double oz, double* partial) {
-    const long long n = (long long)nx * ny * nz;
+__global__ void __launch_bounds__(kDiagX* kDiagY) k_diagnostics(const T* u, int nx, int ny, int nz, int nbuf, T idx,
+                                                               double dx, double ox, double oy, double oz,
+                                                               double* partial) {
     const Vec3<T> U = vec3(u, nx, ny, nz);
+    // tiles of equal size (none larger than 31 x 15 x kDiagZ)
+    const int tx = (nx + gridDim.x - 1) / gridDim.x, ty = (ny + gridDim.y - 1) / gridDim.y,
+              tz = (nz + gridDim.z - 1) / gridDim.z;
+    const int lx = threadIdx.x % kDiagX, ly = threadIdx.x / kDiagX;
+    const int i = (int)blockIdx.x * tx + lx - 1, j = (int)blockIdx.y * ty + ly - 1, k0 = (int)blockIdx.z * tz;
+    const bool own = lx >= 1 && lx <= tx && i < nx && ly >= 1 && ly <= ty && j < ny;
+    __shared__ T e[2][5][kDiagY][kDiagX];  // edge values (1), (2), (3), and the velocities u1, u2
     double acc[kDiagnosticSums];
 #pragma unroll
     for (int v = 0; v < kDiagnosticSums; ++v) acc[v] = 0.0;
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(p % nx);
-        const int j = (int)((p / nx) % ny);
-        const int k = (int)(p / ((long long)nx * ny));
-        const double xi = ox + i * dx, yj = oy + j * dx, zk = oz + k * dx;
-        const double h = 0.5 * dx;
-        // the three edges (i, j, k) and their positions: edge (q) is half a cell back along q
-        const double w[3] = {edge_w(U, 0, i, j, k, nx, ny, nz, idx, nbuf), edge_w(U, 1, i, j, k, nx, ny, nz, idx, nbuf),
-                             edge_w(U, 2, i, j, k, nx, ny, nz, idx, nbuf)};
-        const double pe[3][3] = {{xi - h, yj, zk}, {xi, yj - h, zk}, {xi, yj, zk - h}};
+    const double xi = ox + i * dx, yj = oy + j * dx, h = 0.5 * dx;
+    const bool in_xy = i >= nbuf && j >= nbuf && i < nx - nbuf && j < ny - nbuf && i >= 0 && j >= 0 && i < nx && j < ny;
+    double s0 = 0.0, s1 = 0.0;  // sums over two edges of the plane below, for the cell-centre averages
+    T u2m = (T)0;
+    for (int k = k0 - 1; k < min(k0 + tz, nz); ++k) {
+        T w[3] = {(T)0, (T)0, (T)0};
+        if (in_xy && k >= nbuf && k < nz - nbuf && k >= 0)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int a = (q + 1) % 3, b = (q + 2) % 3;
-            // (x cross w)_q = x_a w_b - x_b w_a, each term at its own edge
-            const double tb = pe[b][a] * w[b], ta = pe[a][b] * w[a];
-            acc[q] += tb - ta;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) acc[3 + 3 * q + c] += tb * pe[b][c] - ta * pe[a][c];
-        }
-        acc[12] += w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-        // cell centre
-        const double uc[3] = {0.5 * ((double)U.c[0](i, j, k) + (double)U.c[0](i - 1, j, k)),
-                              0.5 * ((double)U.c[1](i, j, k) + (double)U.c[1](i, j - 1, k)),
-                              0.5 * ((double)U.c[2](i, j, k) + (double)U.c[2](i, j, k - 1))};
-        const double wc[3] = {
-            0.25 * (w[0] + edge_w(U, 0, i, j - 1, k, nx, ny, nz, idx, nbuf) + edge_w(U, 0, i, j, k - 1, nx, ny, nz, idx, nbuf) +
-                    edge_w(U, 0, i, j - 1, k - 1, nx, ny, nz, idx, nbuf)),
-            0.25 * (w[1] + edge_w(U, 1, i, j, k - 1, nx, ny, nz, idx, nbuf) + edge_w(U, 1, i - 1, j, k, nx, ny, nz, idx, nbuf) +
-                    edge_w(U, 1, i - 1, j, k - 1, nx, ny, nz, idx, nbuf)),
-            0.25 * (w[2] + edge_w(U, 2, i - 1, j, k, nx, ny, nz, idx, nbuf) + edge_w(U, 2, i, j - 1, k, nx, ny, nz, idx, nbuf) +
-                    edge_w(U, 2, i - 1, j - 1, k, nx, ny, nz, idx, nbuf))};
-        const double xc[3] = {xi - h, yj - h, zk - h};
-        const double xw[3] = {xc[1] * wc[2] - xc[2] * wc[1], xc[2] * wc[0] - xc[0] * wc[2],
-                              xc[0] * wc[1] - xc[1] * wc[0]};
-        acc[13] += uc[0] * xw[0] + uc[1] * xw[1] + uc[2] * xw[2];
-        acc[14] += uc[0] * wc[0] + uc[1] * wc[1] + uc[2] * wc[2];
-    }
-    __shared__ double red[kDiagnosticSums][256];
-#pragma unroll
-    for (int v = 0; v < kDiagnosticSums; ++v) red[v][threadIdx.x] = acc[v];
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int v = 0; v < kDiagnosticSums; ++v) red[v][threadIdx.x] += red[v][threadIdx.x + s];
+            for (int q = 0; q < 3; ++q) w[q] = curl_at(U, q, i, j, k, idx);
+        const T u0 = U.c[0](i, j, k), u1 = U.c[1](i, j, k), u2 = U.c[2](i, j, k);
+        T(*p)[kDiagY][kDiagX] = e[k & 1];  // (two sets: one barrier per plane)
+        p[0][ly][lx] = w[0];
+        p[1][ly][lx] = w[1];
+        p[2][ly][lx] = w[2];
+        p[3][ly][lx] = u0;
+        p[4][ly][lx] = u1;
         __syncthreads();
+        if (own) {
+            const double w0 = (double)w[0], w1 = (double)w[1], w2 = (double)w[2];
+            const double t0 = w0 + (double)p[0][ly - 1][lx], t1 = w1 + (double)p[1][ly][lx - 1];
+            if (k >= k0) {
+                const double zk = oz + k * dx;
+                const double we[3] = {w0, w1, w2};
+                const double pe[3][3] = {{xi - h, yj, zk}, {xi, yj - h, zk}, {xi, yj, zk - h}};
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int a = (q + 1) % 3, b = (q + 2) % 3;
+                    // (x cross w)_q = x_a w_b - x_b w_a, each term at its own edge
+                    const double tb = pe[b][a] * we[b], ta = pe[a][b] * we[a];
+                    acc[q] += tb - ta;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) acc[3 + 3 * q + c] += tb * pe[b][c] - ta * pe[a][c];
+                }
+                acc[12] += w0 * w0 + w1 * w1 + w2 * w2;
+                // cell centre
+                const double uc[3] = {0.5 * ((double)u0 + (double)p[3][ly][lx - 1]),
+                                      0.5 * ((double)u1 + (double)p[4][ly - 1][lx]), 0.5 * ((double)u2 + (double)u2m)};
+                const double wc[3] = {0.25 * (t0 + s0), 0.25 * (t1 + s1),
+                                      0.25 * ((w2 + (double)p[2][ly][lx - 1]) +
+                                              ((double)p[2][ly - 1][lx] + (double)p[2][ly - 1][lx - 1]))};
+                const double xc[3] = {xi - h, yj - h, zk - h};
+                const double xw[3] = {xc[1] * wc[2] - xc[2] * wc[1], xc[2] * wc[0] - xc[0] * wc[2],
+                                      xc[0] * wc[1] - xc[1] * wc[0]};
+                acc[13] += uc[0] * xw[0] + uc[1] * xw[1] + uc[2] * xw[2];
+                acc[14] += uc[0] * wc[0] + uc[1] * wc[1] + uc[2] * wc[2];
+            }
+            s0 = t0;
+            s1 = t1;
+            u2m = u2;
+        }
     }
-    if ((int)threadIdx.x < kDiagnosticSums) partial[(long long)blockIdx.x * kDiagnosticSums + threadIdx.x] = red[threadIdx.x][0];
+    // wave sums, then the waves' in order
+    __shared__ double red[kDiagX * kDiagY / 64][kDiagnosticSums];
+#pragma unroll
+    for (int v = 0; v < kDiagnosticSums; ++v) {
+        for (int o = 32; o > 0; o >>= 1) acc[v] += __shfl_xor(acc[v], o);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][v] = acc[v];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < kDiagnosticSums) {
+        double t = 0.0;
+        for (int w = 0; w < kDiagX * kDiagY / 64; ++w) t += red[w][threadIdx.x];
+        const long long b = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+        partial[b * kDiagnosticSums + threadIdx.x] = t;
+    }
 }
 
-// Block weights of the active domain (Sec. 4.3, Eq. weight_fun), one workgroup per block of nb^3
-// cells (blocks tile the box from its origin; the last along an axis may be shorter): mu = the largest
-// |(C u)^(q)| over the block's edges, nu = the largest |Dbar Ntilde(u)| over its cells (nl holds
-// Ntilde(u) on the box), both over the points at least nbuf away from every box face.
+// Block weights of the active domain (Sec. 4.3, Eq. weight_fun) per block of nb^3 cells (blocks tile the
+// box from its origin; the last along an axis may be shorter): mu = the largest |(C u)^(q)| over the block's
+// edges, nu = the largest |Dbar Ntilde(u)| over its cells (Ntilde(u) on the box, zero outside), both over
+// the points at least nbuf away from every box face.
+//
+// A workgroup owns one layer of blocks of a tile of at most 16 x 16 points (whole blocks for nb <= 16, else a
+// part of one block) and walks its planes from one below: Ntilde(u) of the tile and of one more column and
+// row goes through LDS, the plane below stays in registers, so Ntilde(u) never reaches memory.  (A pass for
+// Ntilde and one for the maxima took 94 + 92 us at 192^3 in FP64 with 16^3 blocks; this one 165, bound by
+// the latency of its planes' loads, and it needs no temporary field.)  Parts of one block meet in
+// an atomic maximum, exact in any order (mu and nu start at zero).
+constexpr int kBwTile = 16, kBwThreads = 320;  // 17 x 17 points
 template <typename T>
-__global__ void __launch_bounds__(256) k_block_weights(const T* u, const T* nl, int nx, int ny, int nz, int nb, int nbuf,
-                                                       T idx, double* mu, double* nu) {
+__global__ void __launch_bounds__(kBwThreads) k_block_weights(const T* u, int nx, int ny, int nz, int nb, int nbuf,
+                                                             T idx, int tile, int parts, double* mu, double* nu) {
     const int bxn = (nx + nb - 1) / nb, byn = (ny + nb - 1) / nb;
-    const int b = (int)blockIdx.x;
-    const int bi = b % bxn, bj = (b / bxn) % byn, bk = b / (bxn * byn);
     const Vec3<T> U = vec3(u, nx, ny, nz);
-    const Vec3<T> F = vec3(nl, nx, ny, nz);
+    // whole blocks: tiles side by side; parts of blocks: `parts` tiles per block and axis, the last one shorter
+    const int px = (int)blockIdx.x / parts, py = (int)blockIdx.y / parts, step = parts > 1 ? nb : tile;
+    const int i0 = px * step + ((int)blockIdx.x - px * parts) * tile, j0 = py * step + ((int)blockIdx.y - py * parts) * tile;
+    const int i1 = min(min(px * step + step, i0 + tile), nx), j1 = min(min(py * step + step, j0 + tile), ny);
+    const int k0 = (int)blockIdx.z * nb, k1 = min(k0 + nb, nz);
+    const int ly = (int)threadIdx.x / (kBwTile + 1), lx = (int)threadIdx.x - ly * (kBwTile + 1);
+    const int i = i0 + lx - 1, j = j0 + ly - 1;
+    const bool here = i >= 0 && i < i1 && j >= 0 && j < j1;
+    const bool own = here && lx >= 1 && ly >= 1 && i >= nbuf && j >= nbuf && i < nx - nbuf && j < ny - nbuf;
+    const bool inner = i >= 1 && i < nx - 1 && j >= 1 && j < ny - 1;
+    __shared__ T f[2][2][kBwTile + 1][kBwTile + 1];
+    __shared__ unsigned long long red[2][kBwTile * kBwTile];
+    for (int t = threadIdx.x; t < kBwTile * kBwTile; t += kBwThreads) red[0][t] = red[1][t] = 0ull;
     double m1 = 0.0, m2 = 0.0;
-    const int cells = nb * nb * nb;
-    for (int c = threadIdx.x; c < cells; c += blockDim.x) {
-        const int i = bi * nb + c % nb, j = bj * nb + (c / nb) % nb, k = bk * nb + c / (nb * nb);
-        if (i < nbuf || j < nbuf || k < nbuf || i >= nx - nbuf || j >= ny - nbuf || k >= nz - nbuf) continue;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) m1 = fmax(m1, fabs((double)curl_at(U, q, i, j, k, idx)));
-        const T d = (F.c[0](i, j, k) - F.c[0](i - 1, j, k) + F.c[1](i, j, k) - F.c[1](i, j - 1, k) + F.c[2](i, j, k) -
-                     F.c[2](i, j, k - 1)) * idx;
-        m2 = fmax(m2, fabs((double)d));
-    }
-    __shared__ double r1[256], r2[256];
-    r1[threadIdx.x] = m1;
-    r2[threadIdx.x] = m2;
-    __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            r1[threadIdx.x] = fmax(r1[threadIdx.x], r1[threadIdx.x + s]);
-            r2[threadIdx.x] = fmax(r2[threadIdx.x], r2[threadIdx.x + s]);
+    T below = (T)0;
+    for (int k = max(k0 - 1, 0); k < k1; ++k) {
+        T nl[3] = {(T)0, (T)0, (T)0}, w[3] = {(T)0, (T)0, (T)0};
+        if (here) {
+            if (inner && k >= 1 && k < nz - 1)
+                nonlinear_at(unchecked(U), i, j, k, idx, nl, w);
+            else
+                nonlinear_at(U, i, j, k, idx, nl, w);
+        }
+        T(*p)[kBwTile + 1][kBwTile + 1] = f[k & 1];  // (two sets: one barrier per plane)
+        if (ly <= kBwTile) {
+            p[0][ly][lx] = nl[0];
+            p[1][ly][lx] = nl[1];
         }
         __syncthreads();
+        if (own && k >= k0 && k >= nbuf && k < nz - nbuf) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) m1 = fmax(m1, fabs((double)w[q]));
+            const T d = (nl[0] - p[0][ly][lx - 1] + nl[1] - p[1][ly - 1][lx] + nl[2] - below) * idx;
+            m2 = fmax(m2, fabs((double)d));
+        }
+        below = nl[2];
     }
-    if (threadIdx.x == 0) {
-        mu[b] = r1[0];
-        nu[b] = r2[0];
+    // maxima per block of the tile (bit patterns of nonnegative doubles order like the values)
+    const int per = parts == 1 ? tile / nb : 1;  // blocks per tile and axis
+    if (own) {
+        const int b = parts == 1 ? ((ly - 1) / nb) * per + (lx - 1) / nb : 0;
+        atomicMax(&red[0][b], (unsigned long long)__double_as_longlong(m1));
+        atomicMax(&red[1][b], (unsigned long long)__double_as_longlong(m2));
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < per * per; t += kBwThreads) {
+        const int bi = i0 / nb + t % per, bj = j0 / nb + t / per;
+        if (bi >= bxn || bj >= byn) continue;
+        const long long b = ((long long)blockIdx.z * byn + bj) * bxn + bi;
+        if (parts == 1) {
+            mu[b] = __longlong_as_double((long long)red[0][t]);
+            nu[b] = __longlong_as_double((long long)red[1][t]);
+        } else {
+            atomicMax((unsigned long long*)mu + b, red[0][t]);
+            atomicMax((unsigned long long*)nu + b, red[1][t]);
+        }
     }
 }
 
@@ -636,30 +711,41 @@ int launch_max_abs(int dtype, const void* u, int nbuf, int nx, int ny, int nz, d
 }
 
 int launch_diagnostics(int dtype, const void* u, int nbuf, int nx, int ny, int nz, double dx, const double origin[3],
-                       double* dev_partial, int nblocks, hipStream_t s) {
+                       double* partial, hipStream_t s) {
     if (recording_unsupported()) return NSLGF_OK;
+    const dim3 grid = diag_grid(nx, ny, nz), block(kDiagX * kDiagY);
     if (dtype == NSLGF_F32)
-        hipLaunchKernelGGL(k_diagnostics<float>, dim3(nblocks), dim3(256), 0, s, (const float*)u, nx, ny, nz, nbuf,
-                           (float)(1.0 / dx), dx, origin[0], origin[1], origin[2], dev_partial);
+        hipLaunchKernelGGL(k_diagnostics<float>, grid, block, 0, s, (const float*)u, nx, ny, nz, nbuf, (float)(1.0 / dx),
+                           dx, origin[0], origin[1], origin[2], partial);
     else
-        hipLaunchKernelGGL(k_diagnostics<double>, dim3(nblocks), dim3(256), 0, s, (const double*)u, nx, ny, nz, nbuf,
-                           1.0 / dx, dx, origin[0], origin[1], origin[2], dev_partial);
+        hipLaunchKernelGGL(k_diagnostics<double>, grid, block, 0, s, (const double*)u, nx, ny, nz, nbuf, 1.0 / dx, dx,
+                           origin[0], origin[1], origin[2], partial);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
 
-int launch_block_weights(int dtype, const void* u, const void* nl, int nx, int ny, int nz, int nb, int nbuf, double dx,
-                         double* dev_mu, double* dev_nu, hipStream_t s) {
-    if (recording_unsupported()) return NSLGF_OK;
-    const long long nblocks = (long long)((nx + nb - 1) / nb) * ((ny + nb - 1) / nb) * ((nz + nb - 1) / nb);
-    if (dtype == NSLGF_F32)
-        hipLaunchKernelGGL(k_block_weights<float>, dim3((unsigned)nblocks), dim3(256), 0, s, (const float*)u,
-                           (const float*)nl, nx, ny, nz, nb, nbuf, (float)(1.0 / dx), dev_mu, dev_nu);
-    else
-        hipLaunchKernelGGL(k_block_weights<double>, dim3((unsigned)nblocks), dim3(256), 0, s, (const double*)u,
-                           (const double*)nl, nx, ny, nz, nb, nbuf, 1.0 / dx, dev_mu, dev_nu);
+template <typename T>
+static int block_weights_t(const T* u, int nx, int ny, int nz, int nb, int nbuf, double dx, double* mu, double* nu,
+                           hipStream_t s) {
+    const int parts = ceil_div(nb, kBwTile);
+    const int tile = parts == 1 ? kBwTile / nb * nb : ceil_div(nb, parts);
+    const dim3 grid = parts == 1 ? dim3(ceil_div(nx, tile), ceil_div(ny, tile), ceil_div(nz, nb))
+                                 : dim3(ceil_div(nx, nb) * parts, ceil_div(ny, nb) * parts, ceil_div(nz, nb));
+    if (parts > 1) {
+        const long long nblocks = (long long)ceil_div(nx, nb) * ceil_div(ny, nb) * ceil_div(nz, nb);
+        NSLGF_TRY(launch_zero(NSLGF_F64, mu, nblocks, s));
+        NSLGF_TRY(launch_zero(NSLGF_F64, nu, nblocks, s));
+    }
+    hipLaunchKernelGGL(k_block_weights<T>, grid, dim3(kBwThreads), 0, s, u, nx, ny, nz, nb, nbuf, (T)(1.0 / dx), tile, parts,
+                       mu, nu);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
+}
+int launch_block_weights(int dtype, const void* u, int nx, int ny, int nz, int nb, int nbuf, double dx, double* mu,
+                         double* nu, hipStream_t s) {
+    if (recording_unsupported()) return NSLGF_OK;
+    if (dtype == NSLGF_F32) return block_weights_t<float>((const float*)u, nx, ny, nz, nb, nbuf, dx, mu, nu, s);
+    return block_weights_t<double>((const double*)u, nx, ny, nz, nb, nbuf, dx, mu, nu, s);
 }
 
 int launch_max_speed(int dtype, const void* u, int nx, int ny, int nz, double* dev_partial, int nblocks,
