@@ -204,10 +204,11 @@ int launch_stage_rhs(int dtype, const void* u, const void* q, const void* w1, co
 int launch_masked_div(int dtype, const void* r, void* sdiv, int nbuf, int nx, int ny, int nz, double dx,
                       hipStream_t s);
 // rout = r - G dhat (rout may be r); w_new = (rout - base) * inv  where base = c_q q + c_w1 w1 + c_w2 w2
-// (optional)
+// (optional); dout = dscale dhat (optional)
 int launch_stage_project(int dtype, const void* r, void* rout, const void* dhat, const void* q, const void* w1,
                          const void* w2, double c_q, double c_w1, double c_w2, void* wnew, double inv, int nx, int ny,
-                         int nz, double dx, hipStream_t s, int shape = 0);
+                         int nz, double dx, hipStream_t s, int shape = 0, void* dout = nullptr,
+                         double dscale = 0.0);
 // out = a*x + b*y + c*z (elementwise over n elements; y, z may be null)
 int launch_axpby(int dtype, void* out, const void* x, double a, const void* y, double b, const void* z, double c,
                  long long n, hipStream_t s);

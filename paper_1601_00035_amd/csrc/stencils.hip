@@ -206,6 +206,8 @@ struct StageProjArgs {
     void* wnew;
     double inv, idx;
     int nx, ny, nz;
+    void* dout;  // (optional) dout = dscale dhat
+    double dscale;
 };
 struct AxpbyArgs {
     void* out;
@@ -286,6 +288,7 @@ __global__ void __launch_bounds__(256) k_stage_project(StageProjArgs a0, const S
     NSLGF_CELL_INDEX_Z(bz)
     Fld<T> D{dhat, nx, ny, nz};
     const T d0 = D(i, j, k);
+    if (A.dout) ((T*)A.dout)[idx] = (T)(A.dscale * (double)d0);
     const T g[3] = {(D(i + 1, j, k) - d0) * idx_, (D(i, j + 1, k) - d0) * idx_, (D(i, j, k + 1) - d0) * idx_};
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -653,8 +656,8 @@ int launch_masked_div(int dtype, const void* r, void* sdiv, int nbuf, int nx, in
 
 int launch_stage_project(int dtype, const void* r, void* rout, const void* dhat, const void* q, const void* w1,
                          const void* w2, double c_q, double c_w1, double c_w2, void* wnew, double inv, int nx, int ny,
-                         int nz, double dx, hipStream_t s, int shape) {
-    const StageProjArgs a{r, rout, dhat, q, w1, w2, c_q, c_w1, c_w2, wnew, inv, 1.0 / dx, nx, ny, nz};
+                         int nz, double dx, hipStream_t s, int shape, void* dout, double dscale) {
+    const StageProjArgs a{r, rout, dhat, q, w1, w2, c_q, c_w1, c_w2, wnew, inv, 1.0 / dx, nx, ny, nz, dout, dscale};
     const dim3 grid = cell_grid(nx, ny, nz, 1, shape), block = cell_block(shape);
     if (launch_recorder()) {
         record_launch(dtype == NSLGF_F32 ? &batched_proj<float> : &batched_proj<double>, grid, block, a);
