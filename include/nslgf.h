@@ -198,12 +198,13 @@ int herk_check(nslgf_t h, const nslgf_state *st, int margin, double *div_max, vo
 
 /*
  * One IF-HERK step of each of n independent states (boxes of any supported sizes and dtypes, each
- * with its own u, d and work; none may share them), as one launch: the first call captures the n
- * steps into a HIP graph (of batched passes, or of per-problem branches; see nslgf_set_batch_mode) and
- * later calls with the same states and step parameters replay it.  Results equal n herk_step calls bit
+ * with its own u, d and work; none may share them).  The first call on a batch launches its passes, the
+ * next one on the same states and step parameters captures them into a HIP graph (of batched passes, or of
+ * per-problem branches, which are captured at once; see nslgf_set_batch_mode), and later calls replay the
+ * graph, also after calls on other batches that were not captured.  Results equal n herk_step calls bit
  * for bit.
  * Advances every st->t by its dt.  Builds missing LGF spectra first (synchronising the stream).
- * Guarded states are checked inside the graph and read back after it (one synchronisation); the call
+ * Guarded states are checked inside the step and read back after it (one synchronisation); the call
  * returns NSLGF_ENONFINITE if any of them saw a non-finite value.
  */
 int herk_step_batched(nslgf_t h, nslgf_state *const *sts, int n, void *stream);
@@ -215,8 +216,8 @@ int herk_step_batched(nslgf_t h, nslgf_state *const *sts, int n, void *stream);
  * each problem's arguments from a device table; the groups run on concurrent branch streams.  Steps
  * that use a kernel without a batched form (the step guard, integrating-factor radii above 12) make the
  * call fall back to NSLGF_BATCH_PER_PROBLEM: each state's kernels on a branch stream of its own.
- * nslgf_batch_info reports the last captured graph: *groups (0 for the per-problem form) and *launches
- * (its kernel launches).  Results are identical in both forms.
+ * nslgf_batch_info reports the last batched step: *groups (0 for the per-problem form) and *launches (its
+ * kernel launches).  Results are identical in both forms.
  */
 enum nslgf_batch_mode { NSLGF_BATCH_PASSES = 0, NSLGF_BATCH_PER_PROBLEM = 1 };
 int nslgf_set_batch_mode(nslgf_t h, int mode);

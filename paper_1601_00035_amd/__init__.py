@@ -523,15 +523,15 @@ def set_batch_mode(mode: int, device: int | None = None):
 
 
 def batch_info(device: int | None = None) -> tuple:
-    """(groups, kernel launches) of the last captured batch graph (groups 0: the per-problem form)."""
+    """(groups, kernel launches) of the last batched step (groups 0: the per-problem form)."""
     g, l = ctypes.c_int(), ctypes.c_int()
     _check("nslgf_batch_info", lib().nslgf_batch_info(handle(device), ctypes.byref(g), ctypes.byref(l)))
     return g.value, l.value
 
 
 def herk_step_batched(states: list) -> None:
-    """One step of every state, captured once into a HIP graph and replayed while the batch is
-    unchanged (same boxes, pointers and step parameters)."""
+    """One step of every state: launched pass by pass the first time, captured into a HIP graph the second
+    time and replayed while the batch is unchanged (same boxes, pointers and step parameters)."""
     if not states:
         return
     dev = states[0].u.device

@@ -137,6 +137,24 @@ struct TuneEntry {
     int vy = -1, vz = -1;
 };
 
+// One batch step as recorded: per group of like problems its launches, and the argument tables of them all.
+struct BatchPasses {
+    std::vector<std::vector<int>> groups;          // members (indices of the batch)
+    std::vector<std::vector<LaunchRec>> launches;  // per group: the first member's records
+    std::vector<std::vector<size_t>> off;          // per group and position: offset of its table
+    std::vector<unsigned char> table;
+};
+// Device table of a batch step that is launched without a graph, its pinned source, and when both are free.
+struct BatchSlot {
+    DevBuf dev;
+    HostBuf host;
+    hipEvent_t done = nullptr;
+    bool used = false;
+    ~BatchSlot() {
+        if (done) (void)hipEventDestroy(done);
+    }
+};
+
 // One captured batch step, reused while the batch (boxes, pointers, step parameters) is unchanged.
 struct BatchGraph {
     std::vector<unsigned long long> key;
@@ -154,6 +172,10 @@ struct nslgf_ctx {
     int device = 0;
     nslgf::Profiler prof;
     std::unique_ptr<nslgf::BatchGraph> batch;
+    std::vector<unsigned long long> batch_key;  // the last batch launched without a graph
+    nslgf::BatchSlot batch_slots[4];
+    int batch_slot = 0;
+    int batch_groups = 0, batch_launches = 0;   // of the last batched call
     std::vector<hipStream_t> branches;
     std::vector<hipEvent_t> batch_events;
     hipStream_t capture = nullptr;
@@ -801,13 +823,12 @@ static void tableau(int scheme, double at[4][4], double ct[4]) {
     }
 }
 
-// Records one step of every state (no launch), groups the states whose launch records match position
+// Records one step of every state (no launch) and groups the states whose launch records match position
 // by position (same kernels, grids and blocks: boxes of one size, dtype, scheme and integrating-factor
-// radii), and captures one graph in which every position of every group is one launch over a table of
-// the group's arguments, the groups on their own branch streams.  NSLGF_ESTATE if some step has a
-// launch without a batched form (nothing captured).  Plans, twiddles and launch shapes exist already.
-static int capture_batched_passes(nslgf_ctx* h, nslgf_state* const* sts, int n, hipStream_t s,
-                                  const std::vector<unsigned long long>& key) {
+// radii), so that every position of every group is one launch over a table of the group's arguments.
+// NSLGF_ESTATE if some step has a launch without a batched form.  Plans, twiddles and launch shapes exist
+// already.
+static int record_batch(nslgf_ctx* h, nslgf_state* const* sts, int n, hipStream_t s, BatchPasses* out) {
     std::vector<LaunchRecorder> recs(n);
     bool ok = true;
     const bool prof_was = h->prof.on;
@@ -867,24 +888,27 @@ static int capture_batched_passes(nslgf_ctx* h, nslgf_state* const* sts, int n, 
         groups.swap(split);
     }
     // argument tables: for every group and position, the members' argument structs back to back
-    std::vector<std::vector<size_t>> off(groups.size());
     size_t total = 0;
+    out->off.resize(groups.size());
     for (size_t g = 0; g < groups.size(); ++g)
         for (const LaunchRec& r : recs[groups[g][0]].recs) {
-            off[g].push_back(total);
+            out->off[g].push_back(total);
             total += (r.args.size() * groups[g].size() + 255) / 256 * 256;
         }
-    std::vector<unsigned char> host(std::max<size_t>(total, 256));
+    out->table.assign(std::max<size_t>(total, 256), 0);
     for (size_t g = 0; g < groups.size(); ++g)
-        for (size_t k = 0; k < off[g].size(); ++k)
+        for (size_t k = 0; k < out->off[g].size(); ++k)
             for (size_t m = 0; m < groups[g].size(); ++m) {
                 const LaunchRec& r = recs[groups[g][m]].recs[k];
-                std::memcpy(host.data() + off[g][k] + m * r.args.size(), r.args.data(), r.args.size());
+                std::memcpy(out->table.data() + out->off[g][k] + m * r.args.size(), r.args.data(), r.args.size());
             }
-    auto graph_holder = std::make_unique<BatchGraph>();
-    NSLGF_TRY(graph_holder->desc.ensure(host.size()));
-    NSLGF_HIP_CHECK(hipMemcpy(graph_holder->desc.p, host.data(), host.size(), hipMemcpyHostToDevice));
-    const int nb = std::min((int)groups.size(), 16);
+    for (const std::vector<int>& gr : groups) out->launches.push_back(std::move(recs[gr[0]].recs));
+    out->groups.swap(groups);
+    return NSLGF_OK;
+}
+
+// Branch streams and events for nb concurrent branches.
+static int ensure_branches(nslgf_ctx* h, int nb) {
     while ((int)h->branches.size() < nb) {
         hipStream_t bs;
         NSLGF_HIP_CHECK(hipStreamCreateWithFlags(&bs, hipStreamNonBlocking));
@@ -895,27 +919,44 @@ static int capture_batched_passes(nslgf_ctx* h, nslgf_state* const* sts, int n, 
         NSLGF_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         h->batch_events.push_back(e);
     }
+    return NSLGF_OK;
+}
+
+// Launches a recorded batch step behind `base` (live, or being captured): the groups on branch streams, which
+// join base again.  table: the passes' argument tables on the device.
+static int issue_batch(nslgf_ctx* h, const BatchPasses& b, const void* table, hipStream_t base, int* launches) {
+    const int nb = std::min((int)b.groups.size(), 16);
+    NSLGF_HIP_CHECK(hipEventRecord(h->batch_events[0], base));
+    for (int i = 0; i < nb; ++i) NSLGF_HIP_CHECK(hipStreamWaitEvent(h->branches[i], h->batch_events[0], 0));
+    int rc = NSLGF_OK;
+    *launches = 0;
+    for (size_t g = 0; rc == NSLGF_OK && g < b.groups.size(); ++g)
+        for (size_t k = 0; rc == NSLGF_OK && k < b.launches[g].size(); ++k, ++*launches) {
+            const LaunchRec& r = b.launches[g][k];
+            rc = r.fn((const char*)table + b.off[g][k], (int)b.groups[g].size(), r.grid, r.block, h->branches[g % nb]);
+        }
+    // (joined also after a failed launch: what was launched stays ordered before the caller's next work)
+    for (int i = 0; i < nb; ++i) {
+        NSLGF_HIP_CHECK(hipEventRecord(h->batch_events[i + 1], h->branches[i]));
+        NSLGF_HIP_CHECK(hipStreamWaitEvent(base, h->batch_events[i + 1], 0));
+    }
+    return rc;
+}
+
+// Captures a recorded batch step into h->batch.
+static int capture_batch(nslgf_ctx* h, const BatchPasses& b, const std::vector<unsigned long long>& key) {
+    auto graph_holder = std::make_unique<BatchGraph>();
+    NSLGF_TRY(graph_holder->desc.ensure(b.table.size()));
+    NSLGF_HIP_CHECK(hipMemcpy(graph_holder->desc.p, b.table.data(), b.table.size(), hipMemcpyHostToDevice));
     if (!h->capture) NSLGF_HIP_CHECK(hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking));
     hipGraph_t graph = nullptr;
-    int rc = NSLGF_OK, launches = 0;
+    int launches = 0;
     if (hipStreamBeginCapture(h->capture, hipStreamCaptureModeRelaxed) != hipSuccess) {
+        (void)hipGetLastError();
         set_error("herk_step_batched: stream capture could not start");
-        rc = NSLGF_EHIP;
+        return NSLGF_EHIP;
     }
-    if (rc == NSLGF_OK && hipEventRecord(h->batch_events[0], h->capture) != hipSuccess) rc = NSLGF_EHIP;
-    for (int b = 0; rc == NSLGF_OK && b < nb; ++b)
-        if (hipStreamWaitEvent(h->branches[b], h->batch_events[0], 0) != hipSuccess) rc = NSLGF_EHIP;
-    for (size_t g = 0; rc == NSLGF_OK && g < groups.size(); ++g) {
-        const std::vector<LaunchRec>& rs = recs[groups[g][0]].recs;
-        for (size_t k = 0; rc == NSLGF_OK && k < rs.size(); ++k, ++launches)
-            rc = rs[k].fn((const char*)graph_holder->desc.p + off[g][k], (int)groups[g].size(), rs[k].grid,
-                          rs[k].block, h->branches[g % nb]);
-    }
-    for (int b = 0; rc == NSLGF_OK && b < nb; ++b) {
-        if (hipEventRecord(h->batch_events[b + 1], h->branches[b]) != hipSuccess ||
-            hipStreamWaitEvent(h->capture, h->batch_events[b + 1], 0) != hipSuccess)
-            rc = NSLGF_EHIP;
-    }
+    int rc = issue_batch(h, b, graph_holder->desc.p, h->capture, &launches);
     const hipError_t ec = hipStreamEndCapture(h->capture, &graph);
     if (rc == NSLGF_OK && ec != hipSuccess) {
         set_error(std::string("herk_step_batched: capture failed: ") + hipGetErrorString(ec));
@@ -931,10 +972,29 @@ static int capture_batched_passes(nslgf_ctx* h, nslgf_state* const* sts, int n, 
         return rc;
     }
     graph_holder->key = key;
-    graph_holder->groups = (int)groups.size();
+    graph_holder->groups = (int)b.groups.size();
     graph_holder->launches = launches;
     h->batch = std::move(graph_holder);
     return NSLGF_OK;
+}
+
+// Launches a recorded batch step on s without a graph.  Its tables go through one of four slots, each waited
+// for before it is used again.
+static int launch_batch(nslgf_ctx* h, const BatchPasses& b, hipStream_t s) {
+    BatchSlot& t = h->batch_slots[h->batch_slot];
+    h->batch_slot = (h->batch_slot + 1) % 4;
+    if (t.used) NSLGF_HIP_CHECK(hipEventSynchronize(t.done));
+    t.used = false;
+    if (!t.done) NSLGF_HIP_CHECK(hipEventCreateWithFlags(&t.done, hipEventDisableTiming));
+    NSLGF_TRY(t.dev.ensure(b.table.size()));
+    NSLGF_TRY(t.host.ensure(b.table.size()));
+    std::memcpy(t.host.p, b.table.data(), b.table.size());
+    NSLGF_HIP_CHECK(hipMemcpyAsync(t.dev.p, t.host.p, b.table.size(), hipMemcpyHostToDevice, s));
+    const int rc = issue_batch(h, b, t.dev.p, s, &h->batch_launches);
+    NSLGF_HIP_CHECK(hipEventRecord(t.done, s));
+    t.used = true;
+    h->batch_groups = (int)b.groups.size();
+    return rc;
 }
 
 // Reads a guarded step's accumulators back (synchronising the stream): st->div_max, and
@@ -1283,28 +1343,32 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
                                         (unsigned long long)st->guard, (unsigned long long)st->guard_margin};
         key.insert(key.end(), std::begin(k), std::end(k));
     }
-    if (!h->batch || h->batch->key != key) {
-        h->batch.reset();
-        if (h->batch_mode == NSLGF_BATCH_PASSES) {
-            const int rc = capture_batched_passes(h, sts, n, s, key);
-            if (rc != NSLGF_ESTATE) {  // (NSLGF_ESTATE: a step has no batched form; capture it per problem)
-                NSLGF_TRY(rc);
+    // A batch met for the first time is launched pass by pass; met again right after, it is captured, and from
+    // then on replayed.  (Capturing costs 1.5 to 2.5 ms of host time in which the GPU has nothing to do: callers
+    // that alternate between batches, or build new ones, paid it every time.)
+    bool launched = false;
+    if ((!h->batch || h->batch->key != key) && h->batch_mode == NSLGF_BATCH_PASSES) {
+        BatchPasses passes;
+        int rc = record_batch(h, sts, n, s, &passes);
+        if (rc == NSLGF_OK) {
+            NSLGF_TRY(ensure_branches(h, std::min((int)passes.groups.size(), 16)));
+            if (h->batch_key == key) {
+                h->batch.reset();
+                NSLGF_TRY(capture_batch(h, passes, key));
+            } else {
+                ProfScope ps(h, "batch_graph", s);
+                NSLGF_TRY(launch_batch(h, passes, s));
+                h->batch_key = key;
+                launched = true;
             }
+        } else if (rc != NSLGF_ESTATE) {  // (NSLGF_ESTATE: a step has no batched form; captured per problem below)
+            return rc;
         }
     }
-    if (!h->batch || h->batch->key != key) {
+    if (!launched && (!h->batch || h->batch->key != key)) {
         h->batch.reset();
         const int nb = std::min(n, 16);
-        while ((int)h->branches.size() < nb) {
-            hipStream_t bs;
-            NSLGF_HIP_CHECK(hipStreamCreateWithFlags(&bs, hipStreamNonBlocking));
-            h->branches.push_back(bs);
-        }
-        while ((int)h->batch_events.size() < nb + 1) {
-            hipEvent_t e;
-            NSLGF_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-            h->batch_events.push_back(e);
-        }
+        NSLGF_TRY(ensure_branches(h, nb));
         if (!h->capture) NSLGF_HIP_CHECK(hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking));
         const bool prof_was = h->prof.on;
         h->prof.on = false;
@@ -1347,9 +1411,11 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
         g->key = key;
         h->batch = std::move(g);
     }
-    {
+    if (!launched) {
         ProfScope ps(h, "batch_graph", s);
         NSLGF_HIP_CHECK(hipGraphLaunch(h->batch->exec, s));
+        h->batch_groups = h->batch->groups;
+        h->batch_launches = h->batch->launches;
     }
     int rc = NSLGF_OK;
     for (int i = 0; i < n; ++i) {
@@ -1916,7 +1982,11 @@ int nslgf_copy(nslgf_t h, const void* src, void* dst, size_t n, int dtype, void*
 int nslgf_set_batch_mode(nslgf_t h, int mode) {
     NSLGF_ENTER(h);
     NSLGF_CHECK_ARG(mode == NSLGF_BATCH_PASSES || mode == NSLGF_BATCH_PER_PROBLEM, "nslgf_set_batch_mode: unknown mode");
-    if (mode != h->batch_mode) h->batch.reset();
+    if (mode != h->batch_mode) {
+        h->batch.reset();
+        h->batch_key.clear();
+        h->batch_groups = h->batch_launches = 0;
+    }
     h->batch_mode = mode;
     return NSLGF_OK;
 }
@@ -1924,8 +1994,8 @@ int nslgf_set_batch_mode(nslgf_t h, int mode) {
 int nslgf_batch_info(nslgf_t h, int* groups, int* launches) {
     NSLGF_ENTER(h);
     NSLGF_CHECK_ARG(groups && launches, "nslgf_batch_info: null output");
-    *groups = h->batch ? h->batch->groups : 0;
-    *launches = h->batch ? h->batch->launches : 0;
+    *groups = h->batch_groups;
+    *launches = h->batch_launches;
     return NSLGF_OK;
 }
 

@@ -106,3 +106,26 @@ def test_table_rebuild_recaptures_the_batch_graph():
     torch.cuda.synchronize()
     assert torch.equal(solo.u, st.u) and torch.equal(solo.d, st.d)
     del junk
+
+
+def test_alternating_batches_equal_single_steps():
+    """Two batches in turn (each launched pass by pass), then one repeated (captured, replayed), then the other
+    again: every step equals the single steps, also with the device never waited for in between."""
+    def make(sizes, seed):
+        out = []
+        for i, n in enumerate(sizes):
+            g = torch.Generator().manual_seed(seed + i)
+            u = torch.randn((3, n, n, n), generator=g, dtype=torch.float64).to("cuda:0") * 0.1
+            out.append(nslgf.HerkState(u, 0.1, 0.01, 300.0, "A", n_buf=2))
+        return out
+
+    specs = [((16, 16, 24), 1), ((24, 20), 50)]
+    batched = [make(*sp) for sp in specs]
+    single = [make(*sp) for sp in specs]
+    for b in (0, 1, 0, 1, 1, 1, 0, 1, 0, 0):
+        nslgf.herk_step_batched(batched[b])
+        for st in single[b]:
+            st.step()
+    for x, y in zip(batched, single):
+        for a, b in zip(x, y):
+            assert torch.equal(a.u, b.u) and torch.equal(a.d, b.d) and abs(a.t - b.t) < 1e-15
