@@ -1,16 +1,15 @@
 // Layers of the learned surrogate (a 3D convolutional U-Net) on CDNA4 matrix cores.
 //
 // The 3x3x3 convolutions are implicit GEMMs on v_mfma_f32_32x32x16_bf16 (BF16 operands, FP32
-// accumulation).  One wavefront owns a 32 x 32 output tile and walks the 27 taps and the input
-// channels in steps of 16, gathering its A operand straight from the channels-last activation (the
-// 8 BF16 values a lane supplies are contiguous channels of one voxel) and its B operand from the
-// weight rows.  Operand layout of the instruction (wave64), checked by sur_mfma_selftest:
+// accumulation), 16 input channels a step: the A operand is the channels-last activation (the 8 BF16
+// values a lane supplies are contiguous channels of one voxel), through an LDS halo or straight from
+// memory on small volumes, the B operand the weight rows.  Operand layout of the instruction (wave64), checked by sur_mfma_selftest:
 //   A (32 x 16): lane l supplies A[l % 32][8 (l / 32) + j], j < 8
 //   B (16 x 32): lane l supplies B[8 (l / 32) + j][l % 32]
 //   D (32 x 32): lane l holds D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32] in accumulator i < 16
 // The weight gradient, whose reduction index is the voxel, first copies dY and X into a blocked layout
-// ([voxel / 8][channel][8]: a lane's 8 voxels of one channel are one 16-byte load) and gives each wave
-// the three taps of one (dz, dy) pair, which share their row loads.  It reduces over voxels in fixed
+// ([voxel / 8][channel][8]: a lane's 8 voxels of one channel are one 16-byte word) and gives each wave
+// the three taps of one (dz, dy) pair, over rows staged in an LDS ring.  It reduces over voxels in fixed
 // chunks followed by a fixed-order two-level sum, so every result is deterministic.
 #include <cmath>
 
@@ -50,74 +49,114 @@ __device__ __forceinline__ int tap_dy(int t) { return (t / 3) % 3 - 1; }
 __device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
 
 // Y[v][n] = act(sum_tap sum_k X[v + SIGN off(tap)][k] Wn[tap][n][k]);  K % 16 == 0, N % 32 == 0.
-template <bool RELU, int SIGN>
-__global__ void __launch_bounds__(256) k_conv_mfma(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wn,
-                                                   float* __restrict__ Y, int D, int H, int W, int K, int N) {
-    const int wave = blockIdx.x * 4 + threadIdx.x / 64;
-    const int lane = threadIdx.x % 64;
-    const long long nvox = (long long)D * H * W;
-    const int mtiles = (int)(nvox / 32), ntiles = N / 32;
-    if (wave >= mtiles * ntiles) return;
-    const int mt = wave % mtiles, nt = wave / mtiles;
-    const long long v0 = (long long)mt * 32;
-    const int n0 = nt * 32;
+// A workgroup of 9 wavefronts owns one 32 x 32 output tile; wave g sums the three dx taps of one (dz, dy) pair
+// with its A rows gathered from the activation, and the nine partial tiles are added in LDS in a fixed order.
+// For volumes too small to fill the chip with the LDS-staged kernel below, where a wave's chain of dependent
+// steps is the time: one wave per tile over all 27 taps took 28 us forward and 51 us for the data gradient at
+// 16^3, 96 -> 128 channels, and 27 and 48 us at 8^3; this takes 15 and 22, and 8 and 14.  MT = 2 gives a
+// workgroup two tiles of voxels, which halves its weight reads (19 and 27 us with one at 16^3); below 256
+// tiles that leaves CUs idle (12^3: 10.1 and 14.9 us with one, 10.8 and 20.9 with two).
+__device__ __forceinline__ int split_row(int i, int half) { return 8 * (i / 4) + 4 * half + (i % 4); }
+template <bool RELU, int SIGN, int MT>
+__global__ void __launch_bounds__(576, MT == 1 ? 7 : 5) k_conv_split(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wn,
+                                                    float* __restrict__ Y, int D, int H, int W, int K, int N,
+                                                    long long nblocks) {
+    __shared__ float part[9][MT * 1024];
+    const int ntiles = N / 32;
+    const int g = threadIdx.x / 64, lane = threadIdx.x % 64;
     const int m = lane % 32, half = lane / 32;
-    const long long v = v0 + m;
-    const int x = (int)(v % W), y = (int)((v / W) % H), z = (int)(v / ((long long)W * H));
-    f32x16 acc;
+    const long long nvox = (long long)D * H * W, wtap = (long long)N * K;
+    for (long long blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
+        const int n0 = (int)(blk % ntiles) * 32;
+        const long long v0 = blk / ntiles * (32 * MT);
+        f32x16 acc[MT];
+        const bf16_t* xp[MT][3];
+        bool ok[MT][3];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    // (loading the operands several steps ahead measured slower: the gathered A rows, not load latency,
-    // limit this kernel)
-    for (int tap = 0; tap < 27; ++tap) {
-        const int zz = z + SIGN * tap_dz(tap), yy = y + SIGN * tap_dy(tap), xx = x + SIGN * tap_dx(tap);
-        const bool valid = zz >= 0 && zz < D && yy >= 0 && yy < H && xx >= 0 && xx < W;
-        const long long vn = valid ? ((long long)zz * H + yy) * W + xx : 0;
-        const bf16_t* xrow = X + vn * K + half * 8;
-        const bf16_t* wrow = Wn + ((long long)tap * N + n0 + m) * K + half * 8;
-        for (int kc = 0; kc < K; kc += 16) {
-            const bf16x8 a = valid ? load8(xrow + kc) : zero8();
-            const bf16x8 b = load8(wrow + kc);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+        for (int r = 0; r < MT; ++r) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
+            const long long v = v0 + 32 * r + m;
+            const int x = (int)(v % W), y = (int)((v / W) % H), z = (int)(v / ((long long)W * H));
+            const int zz = z + SIGN * (g / 3 - 1), yy = y + SIGN * (g % 3 - 1);
+            const bool row_ok = v < nvox && zz >= 0 && zz < D && yy >= 0 && yy < H;
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const int xx = x + SIGN * (t - 1);
+                ok[r][t] = row_ok && xx >= 0 && xx < W;
+                xp[r][t] = X + (ok[r][t] ? ((long long)zz * H + yy) * W + xx : 0) * K + half * 8;
+            }
         }
-    }
+        const bf16_t* wp = Wn + ((long long)(3 * g) * N + n0 + m) * K + half * 8;
+#pragma unroll 2
+        for (int kc = 0; kc < K; kc += 16) {
+            bf16x8 a[MT][3], b[3];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int row = 8 * (i / 4) + 4 * half + (i % 4);
-        float val = acc[i];
-        if (RELU) val = fmaxf(val, 0.f);
-        Y[(v0 + row) * N + n0 + m] = val;
+            for (int t = 0; t < 3; ++t) {
+                b[t] = load8(wp + t * wtap + kc);
+#pragma unroll
+                for (int r = 0; r < MT; ++r) a[r][t] = ok[r][t] ? load8(xp[r][t] + kc) : zero8();
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+#pragma unroll
+                for (int r = 0; r < MT; ++r)
+                    acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r][t], b[t], acc[r], 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < MT; ++r)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[g][r * 1024 + i * 64 + lane] = acc[r][i];
+        __syncthreads();
+        for (int e = threadIdx.x; e < MT * 1024; e += 576) {
+            float val = 0.f;
+#pragma unroll
+            for (int w = 0; w < 9; w += 3) val += (part[w][e] + part[w + 1][e]) + part[w + 2][e];
+            if (RELU) val = fmaxf(val, 0.f);
+            const long long v = v0 + e / 1024 * 32 + split_row(e / 64 % 16, (e / 32) % 2);
+            if (v < nvox) Y[v * N + n0 + e % 32] = val;
+        }
+        __syncthreads();
     }
 }
 
-// The same convolution with the input staged in LDS.  A workgroup (4 waves) owns a block of 2 (z) x 8 (y)
-// rows of 32 voxels along x and one tile of 32 output channels (the grid's x index also walks the tiles).  For every slice of 16 input channels it copies the slice's halo (4 x 10 x 34 voxels,
-// zero outside the volume) into LDS once.  Each wave owns 4 adjacent rows of one z plane: for every
-// (dz, dx) of the stencil it reads the 6 halo rows those 4 rows need into registers and applies them for
-// the three dy taps, so that an A operand read from LDS serves up to three taps, and a B operand (weights,
-// read through the caches) serves the wave's 4 rows.  Needs W % 32 == 0, H % 8 == 0, D % 2 == 0.  The sum
-// runs over slices, then dz, dx, dy in a fixed order: results are deterministic.
-constexpr int kLdsBZ = 2, kLdsBY = 8, kLdsHX = 34, kLdsRows = 4;
-constexpr int kLdsHalo = (kLdsBZ + 2) * (kLdsBY + 2) * kLdsHX;  // voxels of the halo block
-template <bool RELU, int SIGN>
+// The same convolution with the input staged in LDS.  A workgroup (4 waves) owns a block of TX x (4 TY) x 4
+// voxels (TX TY = 32) and one tile of 32 output channels.  For every slice of 16 input channels it copies the
+// slice's halo (zero outside the volume) into LDS once; the two 8-channel halves lie in planes of their own,
+// so that a half-wave reads 16-byte words in a row.  Each wave owns TX x TY voxels (its matrix tile) of 4 z
+// planes: for every (dx, dy) of the stencil it reads its tile of the 6 planes those 4 need and applies them
+// for the three dz taps, so that an A operand read from LDS serves up to three taps, and a B operand (weights,
+// read through the caches) serves the wave's 4 planes.  Any volume: voxels beyond it are computed from zeros
+// and not stored.  The sum runs over slices, then dx, dy, dz in a fixed order: results are deterministic.
+// The time is the matrix operations and the latency of a slice's staging and of the weights, which the three
+// workgroups of a CU overlap (128^3, 32 -> 32 channels: 183 to 194 us, 590 to 635 TFLOP/s; a form with the
+// weights in LDS and the next slice in registers ran two workgroups a CU and took 277).  Rows along y served
+// three dy taps before, which tied the block to 32 voxels along x: widths that 32 does not divide went through
+// the gathering kernel (112^3, 32 -> 32: 328 us, now 123; 56^3, 32 -> 64: 81 and 153 for the data gradient,
+// now 39 and 50; 80^3: 121, now 47).
+constexpr int kLdsZ = 4;  // z planes of a workgroup
+template <int TX> struct LdsBlk {
+    static constexpr int TY = 32 / TX, BY = 4 * TY, HX = TX + 2, HY = BY + 2, HZ = kLdsZ + 2;
+    static constexpr int HALO = HX * HY * HZ, PLANE = (HALO + 7) / 8 * 8 + 4;  // (halves 64 bytes apart in the banks)
+};
+template <bool RELU, int SIGN, int TX>
 __global__ void __launch_bounds__(256) k_conv_lds(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wn,
                                                   float* __restrict__ Y, int D, int H, int W, int K, int N) {
-    __shared__ uint4 halo[kLdsHalo * 2];  // [voxel][16 channels] as two 16-byte halves
+    using B = LdsBlk<TX>;
+    __shared__ uint4 halo[2 * B::PLANE];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int m = lane % 32, half = lane / 32;
-    const int xt = W / 32;
-    const int x0 = (blockIdx.x % xt) * 32, nb = (blockIdx.x / xt) * 32;
-    const int y0 = blockIdx.y * kLdsBY, z0 = blockIdx.z * kLdsBZ;
-    // this wave's rows: z = z0 + wave / 2, y = y0 + 4 (wave % 2) + r, r < 4
-    const int tz = wave / 2, ty = kLdsRows * (wave % 2);
-    f32x16 acc[kLdsRows][1];
+    const int xt = (W + TX - 1) / TX;
+    const int x0 = (blockIdx.x % xt) * TX, nb = (blockIdx.x / xt) * 32;
+    const int y0 = blockIdx.y * B::BY, z0 = blockIdx.z * kLdsZ;
+    f32x16 acc[kLdsZ];
 #pragma unroll
-    for (int r = 0; r < kLdsRows; ++r)
+    for (int r = 0; r < kLdsZ; ++r)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[r][0][i] = 0.f;
+        for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
     // this thread's halo elements (the same in every slice): offsets from the block's first voxel, in
-    // BF16 elements (the host keeps 4 H W K below 2^31), and whether each lies inside the volume
-    constexpr int kPer = (kLdsHalo * 2 + 255) / 256, kFirst = kPer / 2;
+    // BF16 elements (the host keeps 6 H W K below 2^31), and whether each lies inside the volume
+    constexpr int kPer = (B::HALO * 2 + 255) / 256, kFirst = kPer / 2;
     const bf16_t* xblk = X + (((long long)z0 * H + y0) * W + x0) * K;
     int hoff[kPer];
     unsigned hok = 0;
@@ -125,11 +164,24 @@ __global__ void __launch_bounds__(256) k_conv_lds(const bf16_t* __restrict__ X, 
     for (int i = 0; i < kPer; ++i) {
         const int q = tid + 256 * i;
         const int hv = q / 2, hh = q % 2;
-        const int hx = hv % kLdsHX, hy = (hv / kLdsHX) % (kLdsBY + 2), hz = hv / (kLdsHX * (kLdsBY + 2));
+        const int hx = hv % B::HX, hy = (hv / B::HX) % B::HY, hz = hv / (B::HX * B::HY);
         const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
         hoff[i] = (((hz - 1) * H + (hy - 1)) * W + (hx - 1)) * K + hh * 8;
-        if (q < kLdsHalo * 2 && xx >= 0 && xx < W && yy >= 0 && yy < H && zz >= 0 && zz < D) hok |= 1u << i;
+        if (q < B::HALO * 2 && xx >= 0 && xx < W && yy >= 0 && yy < H && zz >= 0 && zz < D) hok |= 1u << i;
     }
+    uint4* hdst = halo + (tid % 2) * B::PLANE + tid / 2;
+    const int ty = wave * B::TY + m / TX, tx = m % TX;  // this lane's voxel of the block
+    const uint4* hsrc = halo + half * B::PLANE + (ty + 1) * B::HX + tx + 1;
+    // the weights of the (dx, dy) two ahead are loaded while the current ones multiply, also across slices
+    const bf16_t* wbase = Wn + ((long long)nb + m) * K + half * 8;
+    const long long wtap = (long long)N * K;
+    bf16x8 b[3][3];
+    auto load_b = [&](int kc, int it, bf16x8 (&d)[3]) {
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) d[dz] = load8(wbase + (dz * 9 + it % 3 * 3 + it / 3) * wtap + kc);  // it = 3 dx + dy
+    };
+    load_b(0, 0, b[0]);
+    load_b(0, 1, b[1]);
     for (int kc = 0; kc < K; kc += 16) {
         // the slice's halo in two batches of loads, each issued whole before its LDS writes
         uint4 hr[kFirst];
@@ -138,119 +190,86 @@ __global__ void __launch_bounds__(256) k_conv_lds(const bf16_t* __restrict__ X, 
             hr[i] = (hok >> i) & 1 ? *(const uint4*)(xblk + kc + hoff[i]) : make_uint4(0, 0, 0, 0);
         __syncthreads();  // (the previous slice's reads are done)
 #pragma unroll
-        for (int i = 0; i < kFirst; ++i) halo[tid + 256 * i] = hr[i];
+        for (int i = 0; i < kFirst; ++i) hdst[128 * i] = hr[i];
         uint4 hr2[kPer - kFirst];
 #pragma unroll
         for (int i = kFirst; i < kPer; ++i)
             hr2[i - kFirst] = (hok >> i) & 1 ? *(const uint4*)(xblk + kc + hoff[i]) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int i = kFirst; i < kPer; ++i)
-            if (tid + 256 * i < kLdsHalo * 2) halo[tid + 256 * i] = hr2[i - kFirst];
+            if (tid + 256 * i < B::HALO * 2) hdst[128 * i] = hr2[i - kFirst];
         __syncthreads();
-        // the weights of the next (dz, dx) are loaded while the current ones multiply
-        const bf16_t* wbase = Wn + ((long long)nb + m) * K + kc + half * 8;
-        auto load_b = [&](int it, bf16x8* b) {
-            const int tdz = it / 3 - 1, tdx = it % 3 - 1;
-#pragma unroll
-            for (int tdy = -1; tdy <= 1; ++tdy) {
-                const int tap = (tdz + 1) * 9 + (tdy + 1) * 3 + (tdx + 1);
-                b[tdy + 1] = load8(wbase + (long long)tap * N * K);
-            }
-        };
-        bf16x8 bcur[3], bnext[3];
-        load_b(0, bcur);
+        const int kn = kc + 16 < K ? kc + 16 : kc;  // (after the last slice: loaded and not used)
 #pragma unroll 1
-        for (int it = 0; it < 9; ++it) {
-            if (it + 1 < 9) load_b(it + 1, bnext);
-            const int tdz = it / 3 - 1, tdx = it % 3 - 1;
-            // halo rows ty .. ty + 5 hold the input rows y0 + ty - 1 .. y0 + ty + 4 of plane z + SIGN dz
-            const int hb = ((tz + 1 + SIGN * tdz) * (kLdsBY + 2) + ty) * kLdsHX + (m + 1 + SIGN * tdx);
-            bf16x8 a[kLdsRows + 2];
+        for (int dx = 0; dx < 3; ++dx) {
+            const uint4* hp = hsrc + SIGN * (dx - 1);
 #pragma unroll
-            for (int j = 0; j < kLdsRows + 2; ++j) a[j] = __builtin_bit_cast(bf16x8, halo[(hb + j * kLdsHX) * 2 + half]);
+            for (int dy = 0; dy < 3; ++dy) {
+                const int nx = 3 * dx + dy + 2;
+                load_b(nx < 9 ? kc : kn, nx < 9 ? nx : nx - 9, b[(dy + 2) % 3]);
+                bf16x8 a[kLdsZ + 2];
 #pragma unroll
-            for (int tdy = -1; tdy <= 1; ++tdy)
+                for (int j = 0; j < kLdsZ + 2; ++j)
+                    a[j] = __builtin_bit_cast(bf16x8, hp[j * B::HX * B::HY + SIGN * (dy - 1) * B::HX]);
 #pragma unroll
-                for (int r = 0; r < kLdsRows; ++r)
-                    acc[r][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r + SIGN * tdy + 1], bcur[tdy + 1], acc[r][0], 0, 0, 0);
-            if (it + 1 < 9) {
+                for (int dz = -1; dz <= 1; ++dz)
 #pragma unroll
-                for (int j = 0; j < 3; ++j) bcur[j] = bnext[j];
+                    for (int r = 0; r < kLdsZ; ++r)
+                        acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r + SIGN * dz + 1], b[dy][dz + 1], acc[r], 0, 0, 0);
             }
         }
     }
 #pragma unroll
-    for (int r = 0; r < kLdsRows; ++r) {
-        const long long vrow = ((long long)(z0 + tz) * H + (y0 + ty + r)) * W + x0;
+    for (int r = 0; r < kLdsZ; ++r) {
+        if (z0 + r >= D) break;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int row = 8 * (i / 4) + 4 * half + (i % 4);
-            float val = acc[r][0][i];
+            const int row = split_row(i, half);
+            const int xx = x0 + row % TX, yy = y0 + wave * B::TY + row / TX;
+            float val = acc[r][i];
             if (RELU) val = fmaxf(val, 0.f);
-            Y[(vrow + row) * N + nb + m] = val;
+            if (xx < W && yy < H) Y[(((long long)(z0 + r) * H + yy) * W + xx) * N + nb + m] = val;
         }
     }
 }
 
-// Whether the LDS-staged convolution serves a volume and channel count.
-static bool conv_lds_ok(int D, int H, int W, int K, int N) {
-    return W % 32 == 0 && H % kLdsBY == 0 && D % kLdsBZ == 0 && N % 32 == 0 && N <= 1024 &&
-           4LL * H * W * K < (1LL << 31);
+template <int TX> static long long lds_blocks(int D, int H, int W) {
+    return (long long)ceil_div(W, TX) * ceil_div(H, LdsBlk<TX>::BY) * ceil_div(D, kLdsZ);
 }
-template <bool RELU, int SIGN>
+template <bool RELU, int SIGN, int TX>
 static void launch_conv_lds(const bf16_t* x, const bf16_t* w, float* y, int D, int H, int W, int K, int N,
                             hipStream_t s) {
     // one output tile per workgroup: more workgroups on the small volumes, and more tiles would hold
     // 64 more accumulator registers per lane and tile
-    const dim3 grid((unsigned)(W / 32 * (N / 32)), H / kLdsBY, D / kLdsBZ);
-    hipLaunchKernelGGL((k_conv_lds<RELU, SIGN>), grid, dim3(256), 0, s, x, w, y, D, H, W, K, N);
+    const dim3 grid((unsigned)(ceil_div(W, TX) * (N / 32)), ceil_div(H, LdsBlk<TX>::BY), ceil_div(D, kLdsZ));
+    hipLaunchKernelGGL((k_conv_lds<RELU, SIGN, TX>), grid, dim3(256), 0, s, x, w, y, D, H, W, K, N);
 }
-
-// Partial weight gradient of one voxel chunk: P[chunk][tap][co][ci] = sum_{v in chunk} dY[v][co] X[v+off][ci]
-__global__ void __launch_bounds__(256) k_conv_wgrad(const bf16_t* __restrict__ dY, const bf16_t* __restrict__ X,
-                                                    float* __restrict__ P, int D, int H, int W, int cin, int cout,
-                                                    int chunk_len, int nchunks) {
-    const int wave = blockIdx.x * 4 + threadIdx.x / 64;
-    const int lane = threadIdx.x % 64;
-    const int cotiles = cout / 32, citiles = (cin + 31) / 32;
-    const int total = nchunks * 27 * cotiles * citiles;
-    if (wave >= total) return;
-    int r = wave;
-    const int cit = r % citiles;
-    r /= citiles;
-    const int cot = r % cotiles;
-    r /= cotiles;
-    const int tap = r % 27;
-    const int chunk = r / 27;
-    const int m = lane % 32, half = lane / 32;
-    const int co = cot * 32 + m;   // A row
-    const int ci = cit * 32 + m;   // B column
-    const bool ci_ok = ci < cin;
-    const int dz = tap_dz(tap), dy = tap_dy(tap), dx = tap_dx(tap);
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-    const long long vstart = (long long)chunk * chunk_len;
-    for (long long vb = vstart; vb < vstart + chunk_len; vb += 16) {
-        bf16_t av[8], bv[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const long long v = vb + 8 * half + j;
-            av[j] = dY[v * cout + co];
-            const int x = (int)(v % W), y = (int)((v / W) % H), z = (int)(v / ((long long)W * H));
-            const int zz = z + dz, yy = y + dy, xx = x + dx;
-            const bool ok = ci_ok && zz >= 0 && zz < D && yy >= 0 && yy < H && xx >= 0 && xx < W;
-            bv[j] = ok ? X[(((long long)zz * H + yy) * W + xx) * cin + ci] : (bf16_t)0;
-        }
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pack8(av), pack8(bv), acc, 0, 0, 0);
+// The block shape with the fewest blocks (the least work beyond the volume's edges; 16 wide in a tie: 128^3,
+// 32 -> 32: 194 us forward and 185 for the data gradient, 32 wide 193 and 195, 8 wide 195 and 198).  The split
+// kernel below 48 workgroups, where most CUs would idle over 4 us a slice (16^3, 96 -> 128 with 32 workgroups:
+// 24 us against 15; 24^3, 64 -> 96 with 108: 24 against 39), and where a block's offsets pass 32 bits or the
+// grid its limits.
+template <bool RELU, int SIGN>
+static void launch_conv(const bf16_t* x, const bf16_t* w, float* y, int D, int H, int W, int K, int N, hipStream_t s) {
+    const long long nvox = (long long)D * H * W;
+    const long long b8 = lds_blocks<8>(D, H, W), b16 = lds_blocks<16>(D, H, W), b32 = lds_blocks<32>(D, H, W);
+    long long b = b16;
+    int tx = 16;
+    if (b32 < b) b = b32, tx = 32;
+    if (b8 < b) b = b8, tx = 8;
+    if (b * (N / 32) < 48 || 6LL * H * W * K >= (1LL << 31) || D / kLdsZ >= 65535 || H / 4 >= 65535) {
+        const long long nt = N / 32, tiles = nvox / 32 * nt, pairs = (nvox + 63) / 64 * nt, most = 1 << 22;
+        if (tiles < 256)
+            hipLaunchKernelGGL((k_conv_split<RELU, SIGN, 1>), dim3((unsigned)tiles), dim3(576), 0, s, x, w, y, D, H, W,
+                               K, N, tiles);
+        else
+            hipLaunchKernelGGL((k_conv_split<RELU, SIGN, 2>), dim3((unsigned)(pairs < most ? pairs : most)), dim3(576),
+                               0, s, x, w, y, D, H, W, K, N, pairs);
+        return;
     }
-    if (!ci_ok) return;
-    float* out = P + ((long long)chunk * 27 + tap) * cout * cin;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int row = cot * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-        out[(long long)row * cin + ci] = acc[i];
-    }
+    if (tx == 8) launch_conv_lds<RELU, SIGN, 8>(x, w, y, D, H, W, K, N, s);
+    else if (tx == 16) launch_conv_lds<RELU, SIGN, 16>(x, w, y, D, H, W, K, N, s);
+    else launch_conv_lds<RELU, SIGN, 32>(x, w, y, D, H, W, K, N, s);
 }
 
 // Channels-last [nvox][C] -> blocked [nvox / 8][C][8] (BF16): within each group of 8 consecutive voxels the
@@ -267,6 +286,29 @@ __global__ void __launch_bounds__(256) k_to_blocked8(const bf16_t* __restrict__ 
     uint4 in[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) in[j] = *(const uint4*)(x + (g * 8 + j) * C + cg);
+    const bf16_t* a = (const bf16_t*)in;  // a[j * 8 + c]: voxel j, channel cg + c
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        bf16_t o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = a[j * 8 + c];
+        *(uint4*)(y + (g * C + cg + c) * 8) = *(const uint4*)o;
+    }
+}
+
+// The same layout for rows of W voxels, W % 8 != 0: each x row starts a group of its own and its last group is
+// filled with zeros, [row][ceil(W / 8)][C][8].
+__global__ void __launch_bounds__(256) k_rows_to_blocked8(const bf16_t* __restrict__ x, bf16_t* __restrict__ y,
+                                                          long long rows, int W, int C) {
+    const int cgs = C / 8, nx = (W + 7) / 8;
+    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= rows * nx * cgs) return;
+    const long long g = e / cgs, row = g / nx;
+    const int cg = (int)(e % cgs) * 8, xg = (int)(g % nx) * 8;
+    uint4 in[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        in[j] = xg + j < W ? *(const uint4*)(x + (row * W + xg + j) * C + cg) : make_uint4(0, 0, 0, 0);
     const bf16_t* a = (const bf16_t*)in;  // a[j * 8 + c]: voxel j, channel cg + c
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
@@ -316,112 +358,205 @@ __global__ void __launch_bounds__(256) k_cast_ex(const float* __restrict__ src, 
     }
 }
 
-// Partial weight gradient of one voxel chunk for the three taps of one (dz, dy) pair and one (cout, cin)
-// tile pair:
+// Partial weight gradient of one chunk of the volume and one (cout, cin) tile pair:
 //     P[chunk][tap][co][ci] = sum_{v in chunk} dY[v][co] X[v + off(tap)][ci],  tap = 3 (3 (dz + 1) + dy + 1) + dx + 1,
-// from blocked copies (dYb [nvox / 8][cout][8], Xb [nvox / 8][cin][8]).  One wave per (chunk, tile pair,
-// (dz, dy)); per 16-voxel slice it loads its A operand (dY, 8 voxels per lane) and the three groups of X
-// around x0 (x0 - 8, x0, x0 + 8) once, and forms the B operands of dx = -1, 0, +1 from them.  Small
-// register footprint (three accumulators), so that many waves per SIMD hide the load latency.  Requires
-// W % 8 == 0 (8-voxel groups stay inside one x row).
-__global__ void __launch_bounds__(256) k_conv_wgrad_cm(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb,
-                                                       float* __restrict__ P, int D, int H, int W, int cin, int cout,
-                                                       int chunk_len, int nwaves) {
-    const int wid = blockIdx.x * 4 + threadIdx.x / 64, lane = threadIdx.x % 64;
-    if (wid >= nwaves) return;
+// from blocked copies (dYb [row][nx][cout][8], Xb [row][nx][cin][8], nx groups of 8 voxels a row).  A workgroup of 9
+// wavefronts owns S groups of the rows y0 .. y0 + R - 1 of NZ planes and walks each plane RS rows at a time;
+// wave g takes the three taps of one (dz, dy) pair.  The rows of X lie in an LDS ring (3 planes x 2 RS + 2
+// rows of S groups and one on each side, zero outside the volume) beside two buffers of dY; the rows of the
+// next step are loaded into registers while the current ones multiply.  A half-wave walks SH groups of a
+// row, so that the voxel before and after a group (dx = -1 and +1) come from groups that it holds.
+// PAD: rows of W voxels, W % 8 != 0, filled up with zeros; the one product that would pair such a filler with a
+// voxel of the volume is masked, as are the groups that a half-wave lacks (an infinity there must not count).
+// One workgroup a CU (its LDS, and waves of about 160 registers; the tenth only loads); the time is the matrix
+// operations, 3 of the 9 waves on one SIMD, and a step's LDS latency.  The form before had every wave load its
+// own operands and was bound by L2 (each XCD read all of both tensors for several of the nine pairs): 128^3,
+// 32 -> 32: 276 us with the sums, now 174; 64^3, 32 -> 64: 79, now 63; 112^3: 223, now 144; 56^3, 32 -> 64: 192,
+// now 55; rows that 8 does not divide, gathered voxel by voxel: 12^3, 96 -> 128: 193, now 28.  One row a step: 10 us
+// more at 128^3; two workgroups a CU at 96 registers spilled and took 650.
+constexpr int kWgThreads = 640;
+struct WgradPlan {
+    int nx, S, segs, SH, RS;  // groups of a row and of a segment, segments, groups of a half-wave, rows of a step
+    int R, yb, NZ, zb;        // rows and planes of a chunk, and chunks along y and z
+    int parts;                // partial sums of a chunk
+    int chunks() const { return segs * yb * zb; }
+    size_t lds() const { return (size_t)(3 * (2 * RS + 2) * (2 * SH + 2) + 2 * RS * 2 * SH) * 512; }
+};
+template <int SH, int RS, bool PAD>
+__global__ void __launch_bounds__(kWgThreads)
+k_conv_wgrad_ring(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb, float* __restrict__ P, int D, int H, int W,
+                  int cin, int cout, WgradPlan pl, int nblocks) {
+    extern __shared__ uint4 wg_lds[];
+    constexpr int NR = 2 * RS + 2;
+    constexpr int SP = 2 * SH, S2 = SP + 2;  // groups of the two halves, and with their neighbours
+    constexpr int NX = (3 * RS * S2 * 32 + kWgThreads - 1) / kWgThreads;  // 16-byte words of X of a thread and step
+    // consecutive chunks, which share planes of X, on one XCD
+    const int bid = (int)(blockIdx.x % 8) * ((int)gridDim.x / 8) + (int)blockIdx.x / 8;
+    if (bid >= nblocks) return;
+    const int tid = threadIdx.x, lane = tid % 64, g = tid / 64;
     const int cotiles = cout / 32, citiles = (cin + 31) / 32;
-    int r = wid;
-    const int g = r % 9;  // (dz, dy) = (g / 3 - 1, g % 3 - 1)
-    r /= 9;
+    int r = bid;
     const int cit = r % citiles;
     r /= citiles;
     const int cot = r % cotiles;
     const int chunk = r / cotiles;
+    r = chunk;
+    const int seg = r % pl.segs;
+    r /= pl.segs;
+    const int y0 = (r % pl.yb) * pl.R, y1 = min(H, y0 + pl.R);
+    const int z0 = (r / pl.yb) * pl.NZ, z1 = min(D, z0 + pl.NZ);
+    const int S = pl.S, nx = pl.nx, gx0 = seg * S;
+    const int live = min(S, nx - gx0);  // groups of this segment
+    const bool full = live == SP;
+    uint4* const xr = wg_lds;                  // [plane][ring row][S2][32]
+    uint4* const yr = wg_lds + 3 * NR * S2 * 32;  // [2][RS][SP][32]
     const int dz = g / 3 - 1, dy = g % 3 - 1;
     const int m = lane % 32, half = lane / 32;
-    const int co = cot * 32 + m, ci = cit * 32 + m;
-    const bool ci_ok = ci < cin;
-    const bf16_t* acol = dYb + (long long)co * 8;
-    const bf16_t* bcol = Xb + (long long)(ci_ok ? ci : 0) * 8;
-    const long long astride = (long long)cout * 8, bstride = (long long)cin * 8;
+    // a word of X: group (plane pz, row y, segment group gg - 1), channel ch of the tile
+    auto x_word = [&](int zz, int yy, int gg, int ch) {
+        const int gx = gx0 + gg - 1, ci = cit * 32 + ch;
+        if (zz < 0 || zz >= D || yy < 0 || yy >= H || gx < 0 || gx >= nx || ci >= cin) return make_uint4(0, 0, 0, 0);
+        return *(const uint4*)(Xb + ((((long long)zz * H + yy) * nx + gx) * cin + ci) * 8);
+    };
+    // this thread's words of a step: NX of the RS new rows of X in 3 planes, one of the RS rows of dY.  Of each:
+    // its place in LDS (ring row 0, buffer 0), its place in its row (in words), its row of the step
+    int xdst[NX], xpos[NX];
+    unsigned xoff[NX];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        const int e = tid + kWgThreads * i, ch = e % 32, t = e / 32;
+        const int pz = t / (RS * S2), rr = (t / S2) % RS, gg = t % S2, gx = gx0 + gg - 1, ci = cit * 32 + ch;
+        xdst[i] = (pz * NR * S2 + gg) * 32 + ch;
+        xoff[i] = (unsigned)gx * cin + ci;
+        xpos[i] = t < 3 * RS * S2 ? (gx >= 0 && gx < nx && ci < cin ? 4 * rr + pz : -1) : -2;
+    }
+    const int yt = tid / 32, yrr = yt / SP, ygx = gx0 + yt % SP;
+    const int ydst = 3 * NR * S2 * 32 + tid;
+    const unsigned yoff = (unsigned)ygx * cout + cot * 32 + tid % 32;
+    const bool yhave = yt < RS * SP, yok = yhave && ygx < nx;
+    const unsigned xrow = (unsigned)nx * cin, yrow = (unsigned)nx * cout;  // words of a row
+    auto load_step = [&](int z, int y, uint4 (&w)[NX + 1]) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int zz = z + xpos[i] % 4 - 1, yy = y + 1 + xpos[i] / 4;
+            w[i] = xpos[i] >= 0 && zz >= 0 && zz < D && yy < H
+                       ? ((const uint4*)Xb)[((long long)zz * H + yy) * xrow + xoff[i]]
+                       : make_uint4(0, 0, 0, 0);
+        }
+        w[NX] = yok && y + yrr < y1 ? ((const uint4*)dYb)[((long long)z * H + y + yrr) * yrow + yoff]
+                                    : make_uint4(0, 0, 0, 0);
+    };
+    auto store_step = [&](int y, int buf, const uint4 (&w)[NX + 1]) {
+        const int s0 = (y + 2) % NR;
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            if (xpos[i] == -2) continue;
+            int slot = s0 + (RS == 1 ? 0 : (tid + kWgThreads * i) / 32 / S2 % RS);
+            if (slot >= NR) slot -= NR;
+            wg_lds[xdst[i] + slot * S2 * 32] = w[i];
+        }
+        if (yhave) wg_lds[ydst + buf * RS * SP * 32] = w[NX];
+    };
     f32x16 acc[3];
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
-    // the slice's first voxel as (x, y, z), advanced by 16 voxels per slice without divisions
-    const int vstart = chunk * chunk_len, nslices = chunk_len / 16;
-    int xs = vstart % W, ys = (vstart / W) % H, zs = vstart / (W * H);
-    // operands of one slice: A (dY, 8 voxels of this lane's group) and the X groups at x0 - 8, x0, x0 + 8,
-    // loaded one slice ahead of the matrix operations that use them
-    auto load = [&](int sl, bf16x8& a, uint4& p, uint4& q, uint4& n) {
-        int x0 = xs + 8 * half, y = ys, z = zs;
-        if (x0 >= W) {  // (rows of 8 voxels: the second group starts the next row)
-            x0 -= W;
-            if (++y == H) {
-                y = 0;
-                ++z;
-            }
-        }
-        a = load8(acol + (long long)((vstart >> 3) + 2 * sl + half) * astride);
-        p = make_uint4(0, 0, 0, 0);
-        q = p;
-        n = p;
-        const int zz = z + dz, yy = y + dy;
-        if (ci_ok && zz >= 0 && zz < D && yy >= 0 && yy < H) {
-            const bf16_t* blk = bcol + (long long)(((unsigned)((zz * H + yy) * W + x0)) >> 3) * bstride;
-            q = *(const uint4*)blk;
-            if (x0 >= 8) p = *(const uint4*)(blk - bstride);
-            if (x0 + 8 < W) n = *(const uint4*)(blk + bstride);
-        }
+    // the sums of a long chunk's two halves are partials of their own: half the chain of FP32 additions
+    const int ci = cit * 32 + m;
+    const int steps = (z1 - z0) * ((y1 - y0 + RS - 1) / RS), mid = pl.parts == 2 ? (steps + 1) / 2 : 0;
+    int step = 0, part = chunk * pl.parts;
+    auto put = [&]() {
+        if (ci >= cin || g >= 9) return;
+        int cs = cin;
+        asm volatile("" : "+s"(cs));  // (48 addresses formed here, not held through the loop)
+        float* const out = P + (((long long)part * 27 + 3 * g) * cout + cot * 32 + 4 * half) * cs + ci;
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) out[((long long)t * cout + 8 * (i / 4) + i % 4) * cs] = acc[t][i];
     };
-    bf16x8 a_nx;
-    uint4 p_nx, q_nx, n_nx;
-    load(0, a_nx, p_nx, q_nx, n_nx);
-    for (int sl = 0; sl < nslices; ++sl) {
-        const bf16x8 a = a_nx;
-        const uint4 p = p_nx, q = q_nx, n = n_nx;
-        xs += 16;
-        while (xs >= W) {
-            xs -= W;
-            if (++ys == H) {
-                ys = 0;
-                ++zs;
+    for (int z = z0; z < z1; ++z) {
+        uint4 w[NX + 1];
+        load_step(z, y0, w);
+        __syncthreads();  // (the plane before is done)
+        for (int e = tid; e < 3 * 2 * S2 * 32; e += kWgThreads) {  // rows y0 - 1 and y0
+            const int ch = e % 32, gg = (e / 32) % S2, rr = (e / (32 * S2)) % 2, pz = e / (64 * S2);
+            xr[((pz * NR + (y0 + rr) % NR) * S2 + gg) * 32 + ch] = x_word(z + pz - 1, y0 - 1 + rr, gg, ch);
+        }
+        store_step(y0, 0, w);
+        __syncthreads();
+        int buf = 0;
+        for (int y = y0; y < y1; y += RS, buf ^= 1) {
+            const bool more = y + RS < y1;
+            if (more) load_step(z, y + RS, w);
+#pragma unroll 1
+            for (int rr = 0; rr < RS && y + rr < y1 && g < 9; ++rr) {
+                const uint4* xp = xr + (((dz + 1) * NR + (y + rr + dy + 1) % NR) * S2 + half * SH) * 32 + m;
+                const uint4* ap = yr + ((buf * RS + rr) * SP + half * SH) * 32 + m;
+                unsigned pv = xp[0].w;
+                uint4 q[SH + 1], av[SH];  // this half-wave's groups and the first words of the one after
+#pragma unroll
+                for (int j = 0; j < SH; ++j) {
+                    q[j] = xp[(j + 1) * 32];
+                    av[j] = ap[j * 32];
+                }
+                q[SH].x = xp[(SH + 1) * 32].x;
+#pragma unroll
+                for (int j = 0; j < SH; ++j) {
+                    uint4 c = q[j];
+                    unsigned nv = q[j + 1].x;
+                    if (!full && half * SH + j >= live) {  // (no group here: both operands zero)
+                        c = make_uint4(0, 0, 0, 0);
+                        av[j] = c;
+                        pv = 0;
+                        nv = 0;
+                    }
+                    uint4 bm, bq;  // voxels x0 - 1 .. x0 + 6 and x0 + 1 .. x0 + 8
+                    bm.x = (c.x << 16) | (pv >> 16);
+                    bm.y = (c.y << 16) | (c.x >> 16);
+                    bm.z = (c.z << 16) | (c.y >> 16);
+                    bm.w = (c.w << 16) | (c.z >> 16);
+                    bq.x = (c.x >> 16) | (c.y << 16);
+                    bq.y = (c.y >> 16) | (c.z << 16);
+                    bq.z = (c.z >> 16) | (c.w << 16);
+                    bq.w = (c.w >> 16) | (nv << 16);
+                    pv = c.w;
+                    if (PAD && gx0 + half * SH + j == nx - 1) {  // (the row's last voxel has no neighbour x + 1)
+                        const unsigned keep = W % 2 ? 0xffffu : 0xffff0000u;
+                        if (W % 8 / 2 == 0) bm.x &= keep;
+                        if (W % 8 / 2 == 1) bm.y &= keep;
+                        if (W % 8 / 2 == 2) bm.z &= keep;
+                        if (W % 8 / 2 == 3) bm.w &= keep;
+                    }
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, av[j]);
+                    acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bm), acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, c), acc[1], 0, 0, 0);
+                    acc[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bq), acc[2], 0, 0, 0);
+                }
             }
-        }
-        if (sl + 1 < nslices) load(sl + 1, a_nx, p_nx, q_nx, n_nx);
-        uint4 bm, bp;  // voxels x0 - 1 .. x0 + 6 and x0 + 1 .. x0 + 8 (zero beyond the row)
-        bm.x = (q.x << 16) | (p.w >> 16);
-        bm.y = (q.y << 16) | (q.x >> 16);
-        bm.z = (q.z << 16) | (q.y >> 16);
-        bm.w = (q.w << 16) | (q.z >> 16);
-        bp.x = (q.x >> 16) | (q.y << 16);
-        bp.y = (q.y >> 16) | (q.z << 16);
-        bp.z = (q.z >> 16) | (q.w << 16);
-        bp.w = (q.w >> 16) | (n.x << 16);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bm), acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, q), acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, bp), acc[2], 0, 0, 0);
-    }
-    if (!ci_ok) return;
+            if (more) store_step(y + RS, buf ^ 1, w);
+            if (++step == mid) {
+                put();
+                ++part;
 #pragma unroll
-    for (int t = 0; t < 3; ++t) {
-        float* out = P + ((long long)chunk * 27 + 3 * g + t) * cout * cin;
+                for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = cot * 32 + 8 * (i / 4) + 4 * half + (i % 4);
-            out[(long long)row * cin + ci] = acc[t][i];
+                    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+            }
+            __syncthreads();
         }
     }
+    put();
 }
 
 // First level of the fixed-order chunk reduction: Q[g][i] = sum of the chunks g G .. g G + G - 1.
-__global__ void k_sum_chunk_groups(const float* __restrict__ P, float* __restrict__ Q, long long n, int G) {
+__global__ void k_sum_chunk_groups(const float* __restrict__ P, float* __restrict__ Q, long long n, int G, int nchunks) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int g = blockIdx.y;
     float s = 0.f;
-    for (int c = g * G; c < (g + 1) * G; ++c) s += P[(long long)c * n + i];
+    for (int c = g * G; c < min((g + 1) * G, nchunks); ++c) s += P[(long long)c * n + i];
     Q[(long long)g * n + i] = s;
 }
 
@@ -746,29 +881,56 @@ __global__ void k_mfma_selftest(const bf16_t* A, const bf16_t* B, float* C) {
 
 static int grid1(long long n) { return ceil_div(n, 256); }
 
-// Voxel chunks of the blocked-layout weight gradient: a power of two with chunks of at least 64 voxels
-// (a multiple of 16), enough waves (chunks x tile pairs x 9) to fill the device, at most 4096 chunks.
-// Voxel chunks of the weight gradient: as many as give about `target` waves (each chunk and
-// (dz, dy) pair and channel-tile pair is one wave), chunks of at least 64 voxels (a multiple of 16).
-// Fewer, longer chunks write fewer partials (at 128^3 with 32 -> 32 channels: 2048 chunks wrote
-// 226 MB that the sums read back); measured best: about 4096 waves from 64^3 up, 2048 below.
-static int wgrad_cm_chunks(long long nvox, int cin, int cout) {
-    const long long pairs = (long long)(cout / 32) * ((cin + 31) / 32);
-    const long long target = nvox >= 64LL * 64 * 64 ? 4096 : 2048;
-    int nch = 1;
-    while (nch < 4096 && nch * pairs * 9 < target && nvox % (nch * 2) == 0 && nvox / (nch * 2) >= 64 &&
-           (nvox / (nch * 2)) % 16 == 0)
-        nch *= 2;
-    return nch;
+// Chunks of the weight gradient.  Cost in steps of RS rows (1 to 1.5 us each): the rounds of 256 workgroups
+// (one a CU) times the steps of a chunk, two more for a plane's first rows, and 0.06 a workgroup for its
+// partial sums, written and read once (110 KB).  Chunks of at least 8 rows.  Measured at 80^3, 32 -> 32: 160
+// workgroups of a plane 99 us, what this rule takes 71.
+static WgradPlan wgrad_plan(int D, int H, int W, int cin, int cout) {
+    WgradPlan p;
+    p.nx = ceil_div(W, 8);
+    p.segs = ceil_div(p.nx, 8);
+    p.S = ceil_div(p.nx, p.segs);
+    p.segs = ceil_div(p.nx, p.S);
+    p.SH = (p.S + 1) / 2;
+    p.RS = p.SH >= 3 ? 2 : 4;
+    const long long per = (long long)(cout / 32) * ceil_div(cin, 32) * p.segs;
+    double best = 0;
+    p.R = H;
+    p.NZ = D;
+    for (int yb = 1; yb == 1 || ceil_div(H, yb) >= 8; ++yb) {
+        const int R = ceil_div(ceil_div(H, yb), p.RS) * p.RS;
+        const long long row = per * ceil_div(H, R);
+        for (int rounds = 1; rounds <= 4; ++rounds) {
+            const long long zmax = 256LL * rounds / row;
+            if (zmax < 1 && rounds < 4) continue;
+            const int NZ = zmax < 1 ? D : ceil_div(D, zmax < D ? zmax : D);
+            const long long blocks = row * ceil_div(D, NZ);
+            const double cost = (double)ceil_div(blocks, 256) * NZ * (R / p.RS + 2) + 0.06 * blocks;
+            if (best == 0 || cost < best) {
+                best = cost;
+                p.R = R;
+                p.NZ = NZ;
+            }
+        }
+    }
+    p.yb = ceil_div(H, p.R);
+    p.zb = ceil_div(D, p.NZ);
+    // two partials of a chunk of more than 768 voxels: the error against 64 bits stays at or below that of the
+    // shorter chunks before (128^3: 4.2e-7, with one 5.8e-7), for 8 us of 174
+    p.parts = (long long)p.R * p.NZ * p.S * 8 > 768 ? 2 : 1;
+    return p;
 }
-static bool wgrad_cm_ok(int W, long long nvox) { return W % 8 == 0 && nvox % 16 == 0; }
+// What the blocked form takes as it is: rows of whole groups.
+static bool wgrad_blocked_ok(int W, long long nvox) { return W % 8 == 0 && nvox % 16 == 0; }
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-static int wgrad_chunks(long long nvox) {
-    // voxel chunks of at least 512 (a multiple of 16), at most 64 chunks
-    int nch = 1;
-    while (nch < 64 && nvox / (nch * 2) >= 512 && (nvox / (nch * 2)) % 16 == 0 && nvox % (nch * 2) == 0) nch *= 2;
-    return nch;
+template <int SH, int RS, bool PAD>
+static int launch_wgrad_ring(const WgradPlan& p, const bf16_t* dyc, const bf16_t* xc, float* part, int D, int H, int W,
+                             int cin, int cout, hipStream_t s) {
+    const int blocks = p.chunks() * (cout / 32) * ceil_div(cin, 32);
+    hipLaunchKernelGGL((k_conv_wgrad_ring<SH, RS, PAD>), dim3((unsigned)ceil_div(blocks, 8) * 8), dim3(kWgThreads), p.lds(), s,
+                       dyc, xc, part, D, H, W, cin, cout, p, blocks);
+    return NSLGF_OK;
 }
 
 }  // namespace nslgf
@@ -799,19 +961,11 @@ int sur_conv3d_fwd(nslgf_t h, const void* x, const void* w, void* y, int D, int 
     NSLGF_TRY(conv_shape_ok(D, H, W, cin, cout));
     NSLGF_CHECK_ARG(x && w && y, "sur_conv3d_fwd: null pointer");
     NSLGF_CHECK_ARG(a16(x) && a16(w) && a16(y), "sur_conv3d_fwd: tensors must be 16-byte aligned");
-    const long long waves = (long long)D * H * W / 32 * (cout / 32);
     hipStream_t s = (hipStream_t)stream;
-    if (conv_lds_ok(D, H, W, cin, cout)) {
-        if (relu)
-            launch_conv_lds<true, 1>((const bf16_t*)x, (const bf16_t*)w, (float*)y, D, H, W, cin, cout, s);
-        else
-            launch_conv_lds<false, 1>((const bf16_t*)x, (const bf16_t*)w, (float*)y, D, H, W, cin, cout, s);
-    } else if (relu)
-        hipLaunchKernelGGL((k_conv_mfma<true, 1>), dim3(ceil_div(waves, 4)), dim3(256), 0, s, (const bf16_t*)x,
-                           (const bf16_t*)w, (float*)y, D, H, W, cin, cout);
+    if (relu)
+        launch_conv<true, 1>((const bf16_t*)x, (const bf16_t*)w, (float*)y, D, H, W, cin, cout, s);
     else
-        hipLaunchKernelGGL((k_conv_mfma<false, 1>), dim3(ceil_div(waves, 4)), dim3(256), 0, s, (const bf16_t*)x,
-                           (const bf16_t*)w, (float*)y, D, H, W, cin, cout);
+        launch_conv<false, 1>((const bf16_t*)x, (const bf16_t*)w, (float*)y, D, H, W, cin, cout, s);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
@@ -824,53 +978,49 @@ int sur_conv3d_bwd_data(nslgf_t h, const void* dy, const void* wt, void* dx, int
     NSLGF_CHECK_ARG(dy && wt && dx, "sur_conv3d_bwd_data: null pointer");
     NSLGF_CHECK_ARG(a16(dy) && a16(wt) && a16(dx), "sur_conv3d_bwd_data: tensors must be 16-byte aligned");
     // GEMM with K = cout (inner) and N = cin (outputs), gathering dy at v - off
-    const long long waves = (long long)D * H * W / 32 * (cin / 32);
-    if (conv_lds_ok(D, H, W, cout, cin))
-        launch_conv_lds<false, -1>((const bf16_t*)dy, (const bf16_t*)wt, (float*)dx, D, H, W, cout, cin,
-                                   (hipStream_t)stream);
-    else
-        hipLaunchKernelGGL((k_conv_mfma<false, -1>), dim3(ceil_div(waves, 4)), dim3(256), 0, (hipStream_t)stream,
-                           (const bf16_t*)dy, (const bf16_t*)wt, (float*)dx, D, H, W, cout, cin);
+    launch_conv<false, -1>((const bf16_t*)dy, (const bf16_t*)wt, (float*)dx, D, H, W, cout, cin, (hipStream_t)stream);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
 
+static size_t wgrad_work(int D, int H, int W, int cin, int cout) {
+    // chunk partials, then the group sums of the partials
+    const WgradPlan p = wgrad_plan(D, H, W, cin, cout);
+    const int nch = p.chunks() * p.parts;
+    return align256((size_t)nch * 27 * cin * cout * sizeof(float)) + (size_t)(nch / 32 + 1) * 27 * cin * cout * sizeof(float);
+}
+
 size_t sur_bwd_weight_work_bytes(int D, int H, int W, int cin, int cout) {
-    if (D < 1 || H < 1 || W < 1 || cin < 1 || cout < 1) return 0;
-    const long long nvox = (long long)D * H * W;
-    if (wgrad_cm_ok(W, nvox)) {
-        // the channel-major copies of dY and X, then what the blocked form needs
-        return align256((size_t)nvox * cout * 2) + align256((size_t)nvox * cin * 2) +
-               sur_bwd_weight_blocked_work_bytes(D, H, W, cin, cout);
-    }
-    return (size_t)wgrad_chunks(nvox) * 27 * cin * cout * sizeof(float);
+    if (D < 1 || H < 1 || W < 1 || cin < 1 || cout < 32) return 0;
+    // the blocked copies of dY and X (rows filled up to 8 voxels), then what the blocked form needs
+    const size_t nvox = (size_t)D * H * ceil_div(W, 8) * 8;
+    return align256(nvox * cout * 2) + align256(nvox * cin * 2) + wgrad_work(D, H, W, cin, cout);
 }
 
 size_t sur_bwd_weight_blocked_work_bytes(int D, int H, int W, int cin, int cout) {
-    if (D < 1 || H < 1 || W < 1 || cin < 1 || cout < 1) return 0;
-    const long long nvox = (long long)D * H * W;
-    if (!wgrad_cm_ok(W, nvox)) return 0;
-    // chunk partials, then the group sums of the partials
-    const int nch = wgrad_cm_chunks(nvox, cin, cout);
-    return align256((size_t)nch * 27 * cin * cout * sizeof(float)) + (size_t)(nch / 32 + 1) * 27 * cin * cout * sizeof(float);
+    if (D < 1 || H < 1 || W < 1 || cin < 1 || cout < 32) return 0;
+    if (!wgrad_blocked_ok(W, (long long)D * H * W)) return 0;
+    return wgrad_work(D, H, W, cin, cout);
 }
 
 // Weight gradient from the blocked copies, partials and their fixed-order sums in `work`.
 static int wgrad_from_blocked(const bf16_t* dyc, const bf16_t* xc, float* dw, char* work, int D, int H, int W, int cin,
                               int cout, hipStream_t s) {
-    const long long nvox = (long long)D * H * W;
     const long long n = 27LL * cin * cout;
-    const int nch = wgrad_cm_chunks(nvox, cin, cout);
-    const int chunk_len = (int)(nvox / nch);
+    const WgradPlan p = wgrad_plan(D, H, W, cin, cout);
+    const int nch = p.chunks() * p.parts;
     float* part = (float*)work;
-    const long long nwaves = (long long)nch * (cout / 32) * ((cin + 31) / 32) * 9;
-    hipLaunchKernelGGL(k_conv_wgrad_cm, dim3((unsigned)ceil_div(nwaves, 4)), dim3(256), 0, s, dyc, xc, part, D, H, W,
-                       cin, cout, chunk_len, (int)nwaves);
+    const bool pad = W % 8 != 0;
+#define WGRAD_RING(SH, RS)                                                                          \
+    (pad ? launch_wgrad_ring<SH, RS, true>(p, dyc, xc, part, D, H, W, cin, cout, s)                 \
+         : launch_wgrad_ring<SH, RS, false>(p, dyc, xc, part, D, H, W, cin, cout, s))
+    NSLGF_TRY(p.SH == 4 ? WGRAD_RING(4, 2) : p.SH == 3 ? WGRAD_RING(3, 2) : p.SH == 2 ? WGRAD_RING(2, 4) : WGRAD_RING(1, 4));
+#undef WGRAD_RING
     if (nch >= 64) {
         // two levels (groups of 32 chunks, then the groups), each in a fixed order
-        const int G = 32, ng = nch / G;
+        const int G = 32, ng = ceil_div(nch, G);
         float* q = (float*)(work + align256((size_t)nch * 27 * cin * cout * sizeof(float)));
-        hipLaunchKernelGGL(k_sum_chunk_groups, dim3(grid1(n), ng), dim3(256), 0, s, (const float*)part, q, n, G);
+        hipLaunchKernelGGL(k_sum_chunk_groups, dim3(grid1(n), ng), dim3(256), 0, s, (const float*)part, q, n, G, nch);
         hipLaunchKernelGGL(k_sum_chunks, dim3(grid1(n)), dim3(256), 0, s, (const float*)q, dw, n, ng);
     } else {
         hipLaunchKernelGGL(k_sum_chunks, dim3(grid1(n)), dim3(256), 0, s, (const float*)part, dw, n, nch);
@@ -885,28 +1035,21 @@ int sur_conv3d_bwd_weight(nslgf_t h, const void* dy, const void* x, void* dw, vo
     NSLGF_TRY(conv_shape_ok(D, H, W, cin, cout));
     NSLGF_CHECK_ARG(dy && x && dw && work, "sur_conv3d_bwd_weight: null pointer");
     NSLGF_CHECK_ARG(a16(dy) && a16(x) && a16(dw) && a16(work), "sur_conv3d_bwd_weight: tensors must be 16-byte aligned");
-    const long long nvox = (long long)D * H * W;
+    const long long rows = (long long)D * H, groups = rows * ceil_div(W, 8);
     hipStream_t s = (hipStream_t)stream;
-    const long long n = 27LL * cin * cout;
-    if (wgrad_cm_ok(W, nvox)) {
-        char* base = (char*)work;
-        bf16_t* dyc = (bf16_t*)base;
-        bf16_t* xc = (bf16_t*)(base + align256((size_t)nvox * cout * 2));
-        char* rest = (char*)xc + align256((size_t)nvox * cin * 2);
-        hipLaunchKernelGGL(k_to_blocked8, dim3(ceil_div(nvox / 8 * (cout / 8), 256)), dim3(256), 0, s,
-                           (const bf16_t*)dy, dyc, nvox / 8, cout);
-        hipLaunchKernelGGL(k_to_blocked8, dim3(ceil_div(nvox / 8 * (cin / 8), 256)), dim3(256), 0, s,
-                           (const bf16_t*)x, xc, nvox / 8, cin);
-        return wgrad_from_blocked(dyc, xc, (float*)dw, rest, D, H, W, cin, cout, s);
-    }
-    const int nch = wgrad_chunks(nvox);
-    const int chunk_len = (int)(nvox / nch);
-    const long long waves = (long long)nch * 27 * (cout / 32) * ((cin + 31) / 32);
-    hipLaunchKernelGGL(k_conv_wgrad, dim3(ceil_div(waves, 4)), dim3(256), 0, s, (const bf16_t*)dy, (const bf16_t*)x,
-                       (float*)work, D, H, W, cin, cout, chunk_len, nch);
-    hipLaunchKernelGGL(k_sum_chunks, dim3(grid1(n)), dim3(256), 0, s, (const float*)work, (float*)dw, n, nch);
-    NSLGF_LAUNCH_CHECK();
-    return NSLGF_OK;
+    bf16_t* dyc = (bf16_t*)work;
+    bf16_t* xc = (bf16_t*)((char*)work + align256((size_t)groups * 8 * cout * 2));
+    char* rest = (char*)xc + align256((size_t)groups * 8 * cin * 2);
+    auto blocked = [&](const void* src, bf16_t* dst, int c) {
+        const dim3 grid((unsigned)ceil_div(groups * (c / 8), 256));
+        if (W % 8 == 0)
+            hipLaunchKernelGGL(k_to_blocked8, grid, dim3(256), 0, s, (const bf16_t*)src, dst, groups, c);
+        else
+            hipLaunchKernelGGL(k_rows_to_blocked8, grid, dim3(256), 0, s, (const bf16_t*)src, dst, rows, W, c);
+    };
+    blocked(dy, dyc, cout);
+    blocked(x, xc, cin);
+    return wgrad_from_blocked(dyc, xc, (float*)dw, rest, D, H, W, cin, cout, s);
 }
 
 int sur_conv3d_bwd_weight_blocked(nslgf_t h, const void* dyb, const void* xb, void* dw, void* work, int D, int H, int W,
@@ -915,7 +1058,7 @@ int sur_conv3d_bwd_weight_blocked(nslgf_t h, const void* dyb, const void* xb, vo
     NSLGF_TRY(conv_shape_ok(D, H, W, cin, cout));
     NSLGF_CHECK_ARG(dyb && xb && dw && work, "sur_conv3d_bwd_weight_blocked: null pointer");
     NSLGF_CHECK_ARG(a16(dyb) && a16(xb) && a16(dw) && a16(work), "sur_conv3d_bwd_weight_blocked: tensors must be 16-byte aligned");
-    NSLGF_CHECK_ARG(wgrad_cm_ok(W, (long long)D * H * W), "sur_conv3d_bwd_weight_blocked: needs W % 8 == 0 and D*H*W % 16 == 0");
+    NSLGF_CHECK_ARG(wgrad_blocked_ok(W, (long long)D * H * W), "sur_conv3d_bwd_weight_blocked: needs W % 8 == 0 and D*H*W % 16 == 0");
     return wgrad_from_blocked((const bf16_t*)dyb, (const bf16_t*)xb, (float*)dw, (char*)work, D, H, W, cin, cout,
                               (hipStream_t)stream);
 }

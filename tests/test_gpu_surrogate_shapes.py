@@ -1,0 +1,63 @@
+"""Convolutions and weight gradients at the edges of their blocks: halo blocks 8, 16 and 32 voxels wide with
+remainders on every axis, the split kernel with one and two tiles, row segments of 1 to 8 groups of 8 voxels
+(odd counts, a shorter last segment, rows that 8 does not divide) and chunks of several planes."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1601_00035_amd.surrogate as S
+from oracle import conv3d as C
+from test_gpu_surrogate import DEV, rand_bf16, rel, to_bf16_bits
+
+pytestmark = pytest.mark.gpu
+
+# (D, H, W), cin, cout.  Tolerance: FP32 sums of at most 27 * 1024 products of BF16 values against FP64:
+# relative to the norm, below sqrt(n) eps = 1e-5.
+SHAPES = [
+    ((8, 14, 40), 16, 256), ((12, 16, 8), 16, 512), ((4, 12, 32), 16, 512), ((4, 12, 30), 32, 512),
+    ((5, 8, 36), 32, 256), ((5, 9, 32), 32, 32), ((9, 32, 7), 64, 32), ((2, 16, 1), 16, 32), ((1, 32, 9), 32, 32),
+    ((3, 32, 20), 16, 32), ((2, 16, 72), 32, 32), ((1, 16, 130), 32, 32), ((33, 4, 16), 32, 64), ((3, 32, 56), 32, 32),
+    ((32, 37, 8), 32, 32), ((40, 5, 48), 48, 32),
+]
+
+
+@pytest.mark.parametrize("dims,cin,cout", SHAPES)
+def test_block_edges(dims, cin, cout):
+    D, H, W = dims
+    nv = D * H * W
+    x, w, gy = rand_bf16((D, H, W, cin), 3), rand_bf16((27, cout, cin), 4, 0.1), rand_bf16((D, H, W, cout), 5)
+    xb, wb, gb = to_bf16_bits(x), to_bf16_bits(w), to_bf16_bits(gy)
+    y = torch.full((nv * cout,), float("nan"), dtype=torch.float32, device=DEV)
+    S.call("sur_conv3d_fwd", xb, wb, y, D, H, W, cin, cout, 0)
+    ref = C.conv_fwd(x, w)
+    assert rel(y.double().cpu().numpy().reshape(ref.shape), ref) < 1e-5
+    work = torch.full((S.lib().sur_bwd_weight_work_bytes(D, H, W, cin, cout) // 4 + 1,), float("nan"), device=DEV)
+    gw = torch.full((27 * cout * cin,), float("nan"), dtype=torch.float32, device=DEV)
+    S.call("sur_conv3d_bwd_weight", gb, xb, gw, work, D, H, W, cin, cout)
+    refw = C.conv_bwd_weight(gy, x)
+    assert rel(gw.double().cpu().numpy().reshape(refw.shape), refw) < 1e-5
+    if cin % 32 == 0:
+        wt = S.bf16_empty(w.size, DEV)
+        S.call("sur_weight_transpose", wb, wt, cin, cout)
+        gx = torch.full((nv * cin,), float("nan"), dtype=torch.float32, device=DEV)
+        S.call("sur_conv3d_bwd_data", gb, wt, gx, D, H, W, cin, cout)
+        refx = C.conv_bwd_data(gy, w)
+        assert rel(gx.double().cpu().numpy().reshape(refx.shape), refx) < 1e-5
+
+
+@pytest.mark.parametrize("W", [12, 40, 72])
+def test_infinity_counts_in_its_own_taps_only(W):
+    """An infinite input in a row's last voxel reaches the taps that pair it with a voxel of the volume."""
+    D, H, cin, cout = 2, 16, 32, 32
+    x, gy = rand_bf16((D, H, W, cin), 3), rand_bf16((D, H, W, cout), 5)
+    x[0, 3, W - 1, 0] = np.inf
+    gy[gy == 0] = 1.0
+    work = torch.empty(S.lib().sur_bwd_weight_work_bytes(D, H, W, cin, cout) // 4 + 1, device=DEV)
+    gw = torch.empty(27 * cout * cin, dtype=torch.float32, device=DEV)
+    S.call("sur_conv3d_bwd_weight", to_bf16_bits(gy), to_bf16_bits(x), gw, work, D, H, W, cin, cout)
+    bad = ~torch.isfinite(gw.reshape(27, cout, cin)).cpu().numpy()
+    want = np.zeros_like(bad)
+    for t in range(27):  # partner v - off: z = -dz, y = 3 - dy, x = W - 1 - dx
+        dz, dy, dx = t // 9 - 1, t // 3 % 3 - 1, t % 3 - 1
+        want[t, :, 0] = 0 <= -dz < D and 0 <= 3 - dy < H and W - 1 - dx < W
+    assert np.array_equal(bad, want)
