@@ -266,6 +266,14 @@ __device__ __forceinline__ void pass_load(cplx<T>* v, int t, Acc& acc) {
     }
 }
 
+// Orders a wave's LDS writes before its own later reads at other lanes' addresses (LDS serves a wave's
+// instructions in order; this only keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// (The TP threads of a transform are lanes of one wave, so its exchanges need no workgroup barrier.)
 template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, class RL> struct Runner;
 
 template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, int R>
@@ -282,10 +290,11 @@ template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, int R, 
 struct Runner<T, L, E, TP, INV, NS, PRUNE, RList<R, R2, Rest...>> {
     template <class Acc>
     __device__ __forceinline__ static void run(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc& acc) {
+        static_assert(64 % TP == 0, "a transform's threads must be lanes of one wave");
         pass_compute<T, L, E, TP, INV, NS, R, (NS == 1) ? (PRUNE & 1) : 0>(v, t, tw);
-        __syncthreads();
+        wave_sync();
         pass_store<T, L, E, TP, NS, R>(v, t, acc);
-        __syncthreads();
+        wave_sync();
         pass_load<T, L, E, TP, R2>(v, t, acc);
         Runner<T, L, E, TP, INV, NS * R, PRUNE, RList<R2, Rest...>>::run(v, t, tw, acc);
     }

@@ -49,14 +49,14 @@ __global__ void __launch_bounds__(256) k_row_r2c(RowPass a0, const RowPass* __re
     __shared__ cplx<T> lds[RPW * LD];
     const int tid = threadIdx.x;
     const int rl = tid / TP, t = tid % TP;
-    const long long row = (long long)blockIdx.x * RPW + rl;
+    const long long row = (long long)blockIdx.x * (blockDim.x / TP) + rl;
     const int comp = blockIdx.y;
     const bool valid = row < a.nrows;
     const T* in = (const T*)a.in + comp * a.in_comp + (valid ? row : 0) * a.in_row;
     cplx<T>* out = (cplx<T>*)a.out + comp * a.out_comp + (valid ? row : 0) * a.out_row;
     // the half-length root table goes to LDS (read by the transform's passes after the barrier below)
     __shared__ cplx<T> twh[LH];
-    for (int m = tid; m < LH; m += RPW * TP) twh[m] = ((const cplx<T>*)a.tw_half)[m];
+    for (int m = tid; m < LH; m += blockDim.x) twh[m] = ((const cplx<T>*)a.tw_half)[m];
     const cplx<T>* twf = (const cplx<T>*)a.tw_full;
     RowAcc<T> acc{lds + rl * LD};
     cplx<T> v[E];
@@ -91,14 +91,14 @@ __global__ void __launch_bounds__(256) k_row_r2c(RowPass a0, const RowPass* __re
     __syncthreads();
     fft_regs<T, LH, false, RL>(v, t, twh, acc);
     constexpr int RLs = Last<RL>::value;
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int b = 0; b < E / RLs; ++b) {
         const int j = t + b * TP;
 #pragma unroll
         for (int r = 0; r < RLs; ++r) acc(j + r * (LH / RLs)) = v[b * RLs + r];
     }
-    __syncthreads();
+    wave_sync();
     if (valid) {
         // X[k] = E[k] + W_P^k O[k], E = (Z[k] + conj Z[-k]) / 2, O = -i (Z[k] - conj Z[-k]) / 2
         for (int k = t; k < LH; k += TP) {
@@ -128,13 +128,13 @@ __global__ void __launch_bounds__(256) k_row_c2r(RowPass a0, const RowPass* __re
     __shared__ cplx<T> lds[RPW * LD];
     const int tid = threadIdx.x;
     const int rl = tid / TP, t = tid % TP;
-    const long long row = (long long)blockIdx.x * RPW + rl;
+    const long long row = (long long)blockIdx.x * (blockDim.x / TP) + rl;
     const int comp = blockIdx.y;
     const bool valid = row < a.nrows;
     const cplx<T>* in = (const cplx<T>*)a.in + comp * a.in_comp + (valid ? row : 0) * a.in_row;
     T* out = (T*)a.out + comp * a.out_comp + (valid ? row : 0) * a.out_row;
     __shared__ cplx<T> twh[LH];  // the half-length root table, in LDS from the first barrier on
-    for (int m = tid; m < LH; m += RPW * TP) twh[m] = ((const cplx<T>*)a.tw_half)[m];
+    for (int m = tid; m < LH; m += blockDim.x) twh[m] = ((const cplx<T>*)a.tw_half)[m];
     const cplx<T>* twf = (const cplx<T>*)a.tw_full;
     RowAcc<T> acc{lds + rl * LD};
     for (int k = t; k <= LH; k += TP) acc(k) = valid ? in[k] : mk<T>((T)0, (T)0);
@@ -290,8 +290,16 @@ template <typename T, int L, int MODE, bool HALF> static int issue_col(const Col
 template <typename T> static bool real_pairs(const void* p, long long row, long long comp, int n_io) {
     return ((uintptr_t)p % (2 * sizeof(T))) == 0 && row % 2 == 0 && comp % 2 == 0 && n_io % 2 == 0;
 }
-template <typename T, int LH> static int do_r2c(const RowPass& a, hipStream_t s) {
+// Rows of a workgroup: one wave's worth where the launch is at most a wave a SIMD, so that it spreads over the
+// CUs (32^3 solve, 64 waves: the two row passes 5.2 and 5.6 us in workgroups of four waves with a barrier at each
+// exchange, 4.6 and 4.8 so, where the exchanges are a wave's own); full workgroups share the twiddle table.
+template <typename T, int LH> static int row_rows(const RowPass& a) {
     constexpr int TP = LH / Plan1D<LH>::E, RPW = row_rpw<T, LH>();
+    return a.nrows * a.ncomp * TP <= 1024 * 64 && RPW > 64 / TP ? 64 / TP : RPW;
+}
+template <typename T, int LH> static int do_r2c(const RowPass& a, hipStream_t s) {
+    constexpr int TP = LH / Plan1D<LH>::E;
+    const int RPW = row_rows<T, LH>(a);
     dim3 grid(ceil_div(a.nrows, RPW), a.ncomp);
     if (a.div_src) {
         if (a.ncomp != 1 || a.nrows != (long long)a.div_ny * a.div_nz) {
@@ -304,7 +312,8 @@ template <typename T, int LH> static int do_r2c(const RowPass& a, hipStream_t s)
     return issue_r2c<T, LH, false, false>(a, grid, dim3(RPW * TP), s);
 }
 template <typename T, int LH> static int do_c2r(const RowPass& a, hipStream_t s) {
-    constexpr int TP = LH / Plan1D<LH>::E, RPW = row_rpw<T, LH>();
+    constexpr int TP = LH / Plan1D<LH>::E;
+    const int RPW = row_rows<T, LH>(a);
     dim3 grid(ceil_div(a.nrows, RPW), a.ncomp);
     const bool pairs = real_pairs<T>(a.out, a.out_row, a.out_comp, a.n_io);
     if (launch_recorder()) {

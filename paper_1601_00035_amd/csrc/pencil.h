@@ -63,13 +63,6 @@ template <typename T> struct alignas(16) Slot {
     cplx<T> c[sizeof(T) == 8 ? 1 : 2];
 };
 
-// Orders a wave's LDS writes before its own later reads at other lanes' addresses (LDS serves a wave's
-// instructions in order; this only keeps the compiler from moving them).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <typename T, int R, bool INV, int PRUNE = 0> __device__ __forceinline__ void dft(cplx<T>* v) {
     if constexpr (R == 1) {
     } else if constexpr (PRUNE == 1) {
