@@ -61,3 +61,24 @@ def test_infinity_counts_in_its_own_taps_only(W):
         dz, dy, dx = t // 9 - 1, t // 3 % 3 - 1, t % 3 - 1
         want[t, :, 0] = 0 <= -dz < D and 0 <= 3 - dy < H and W - 1 - dx < W
     assert np.array_equal(bad, want)
+
+
+@pytest.mark.parametrize("nv,c", [(8, 8), (120, 24), (136, 40), (256, 96), (1032, 32)])
+@pytest.mark.parametrize("use_act", [False, True])
+def test_cast_tiles(nv, c, use_act):
+    """Tiles of 128 voxels x 32 channels with remainders, bit for bit the separate casts (NaN and infinities too)."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    src = torch.randn(nv * c, generator=g, device=DEV)
+    src[::17], src[5::31] = float("inf"), float("nan")
+    act = torch.randn(nv * c, generator=g, device=DEV)
+    act[::13] = float("nan")
+    ref, ref_b, ref_k = src.clone(), S.bf16_empty(nv * c, DEV), S.bf16_empty(nv * c, DEV)
+    if use_act:
+        S.call("sur_relu_bwd", act, ref, nv * c)
+    S.call("sur_cast_bf16", ref, ref_b, nv * c)
+    S.call("sur_to_blocked8", ref_b, ref_k, nv, c)
+    for blocked in (True, False):
+        y, yk = (torch.full((nv * c,), 77, dtype=torch.int16, device=DEV) for _ in range(2))
+        S.call("sur_cast_bf16_ex", src, act if use_act else None, y, yk if blocked else None, nv, c)
+        assert torch.equal(y.view(torch.int16), ref_b.view(torch.int16))
+        assert torch.equal(yk, ref_k.view(torch.int16) if blocked else torch.full_like(yk, 77))
