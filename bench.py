@@ -57,9 +57,10 @@ def alg_bytes_per_step(N: int, P: int, es: int) -> dict:
         "if_xy": (15 * 2 + 6 + 9 + 12) * n3 * es,
         "if_z": 15 * 2 * n3 * es,
         "curl_bar": 6 * n3 * es,
-        "stage_rhs": 30 * n3 * es,
-        "stage_project": 7 * n3 * es,  # the last stage only (H^3 = I): reads r, dhat, writes u
-        "axpby": 2 * n3 * es,
+        # stage 1 reads u (which is q^1) and writes r; stage 2 reads q and w^{1,1} too, stage 3 updates r
+        "stage_rhs": 27 * n3 * es,
+        # the last stage only (H^3 = I): reads r, dhat, writes u and the scaled pressure
+        "stage_project": 8 * n3 * es,
     }
 
 
@@ -258,7 +259,7 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-secondary", action="store_true")
     ap.add_argument("--fft-plan", type=int, default=-1, choices=(-1, 0, 1, 2),
-                    help="column-pass FFT radix plan: -1 default, 0 narrow, 1 wide, 2 narrow on fewer elements")
+                    help="column-pass FFT plan number (-1 default; the numbers 0 to 2 all name the one column pass)")
     ap.add_argument("--calibrate", action="store_true",
                     help="first copy 1 GiB with the library's plain copy kernel (reference for byte counters)")
     args = ap.parse_args()
