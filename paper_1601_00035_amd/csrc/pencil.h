@@ -103,14 +103,16 @@ k_pencil(ColPass a0, const ColPass* __restrict__ da, int per) {
         tile = rest / a.nouter;
         outer = (sq & 1) ? a.nouter - 1 - (sq >> 1) : (sq >> 1);
     } else {
-        // Consecutive workgroups go to different XCDs.  The forward pass writes twice what it reads: groups of
-        // 4 tiles (512 bytes of every row) on one XCD make it 6 % faster (531 -> 501 us, three FP64 components
-        // at 256^3); the inverse gains nothing and keeps the plain order.
+        // Consecutive workgroups go to different XCDs.  The forward pass writes twice what it reads: on launches
+        // beyond the caches, groups of 4 tiles (512 bytes of every row) on one XCD make it 6 % faster (531 -> 501 us,
+        // three FP64 components at 256^3, the solve 2348 -> 2340 us); on small ones they leave XCDs idle (54 x 26 x 79,
+        // three components: 10.0 us grouped, 5.2 in the plain order), and at 128^3 to 192^3 the two are alike.  The
+        // inverse gains nothing and keeps the plain order.
         constexpr int GRP = MODE == COL_FWD ? 4 : 1;
         const int nt = (int)gridDim.x, n = nt * (int)gridDim.y * (int)gridDim.z;
         int lg = (int)blockIdx.x + nt * ((int)blockIdx.y + (int)gridDim.y * (int)blockIdx.z);
         const int g = lg / (8 * GRP), r = lg % (8 * GRP);
-        if ((g + 1) * 8 * GRP <= n) lg = g * 8 * GRP + (r % 8) * GRP + r / 8;
+        if (n >= 8192 && (g + 1) * 8 * GRP <= n) lg = g * 8 * GRP + (r % 8) * GRP + r / 8;
         tile = lg % nt;
         lg /= nt;
         outer = lg % (int)gridDim.y;
