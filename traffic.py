@@ -163,11 +163,11 @@ def surrogate_summary(run_dir: str, n: int, iters: int) -> str:
 
     def kind(name):
         short = name.split("(")[0]
-        if "k_conv_lds<" in short or "k_conv_mfma<" in short:
-            return "dgrad" if short.rstrip(">").endswith("-1") else "fwd"
+        if "k_conv_lds<" in short or "k_conv_split<" in short:
+            return "dgrad" if ", -1," in short else "fwd"
         if "k_conv_wgrad" in short:
             return "wgrad"
-        if "k_to_blocked8" in short:
+        if "to_blocked8" in short:
             return "pre"
         if "k_sum_chunk" in short:
             return "post"
