@@ -201,18 +201,19 @@ template <typename T, int MODE> struct IfOperands {
 };
 template <typename T, int MODE>
 __device__ __forceinline__ void if_load(IfOperands<T, MODE>& o, const T* __restrict__ in, const IfTerms& t, int comp,
-                                        int z, int x, int y, int nx, int ny, int nz, bool inside, bool owned) {
+                                        int z, int x, int y, int nx, int ny, int nz, long long pbase, bool inside,
+                                        bool owned) {
 #pragma unroll
     for (int i = 0; i < IfOperands<T, MODE>::N; ++i) o.v[i] = (T)0;
     if (!inside) return;
-    const long long c0 = ((long long)z * ny + y) * nx + x;  // offset within one component
-    const long long e = (long long)comp * nx * ny * nz + c0;
+    const long long yx = (long long)y * nx + x, e = pbase + yx;  // (pbase: the plane's first element)
     o.v[0] = in[e];
     if constexpr (MODE == IF_IN_COMB) {
         o.v[1] = ((const T*)t.in1)[e];
         if (t.in2) o.v[2] = ((const T*)t.in2)[e];
     } else if constexpr (MODE == IF_IN_PROJ) {
         const T* D = (const T*)t.dhat;
+        const long long c0 = (long long)z * ny * nx + yx;  // offset within one component
         o.v[1] = D[c0];
         const bool has = comp == 0 ? x + 1 < nx : comp == 1 ? y + 1 < ny : z + 1 < nz;
         const long long step = comp == 0 ? 1 : comp == 1 ? nx : (long long)nx * ny;
@@ -225,7 +226,7 @@ __device__ __forceinline__ void if_load(IfOperands<T, MODE>& o, const T* __restr
 }
 template <typename T, int MODE>
 __device__ __forceinline__ T if_value(const IfOperands<T, MODE>& o, const IfTerms& t, int comp, int z, int x, int y,
-                                      int nx, int ny, int nz, bool inside, bool owned) {
+                                      int nx, int ny, int nz, long long pbase, bool inside, bool owned) {
     if constexpr (MODE == IF_IN_COMB) {
         double v = t.c0 * (double)o.v[0];
         v += t.c1 * (double)o.v[1];
@@ -236,7 +237,7 @@ __device__ __forceinline__ T if_value(const IfOperands<T, MODE>& o, const IfTerm
         if (t.wnew && inside && owned) {
             double base = t.c_q * (double)o.v[3];
             if (t.w1) base += t.c_w1 * (double)o.v[4];
-            ((T*)t.wnew)[(((long long)comp * nz + z) * ny + y) * nx + x] = (T)(((double)v - base) * t.inv);
+            ((T*)t.wnew)[pbase + (long long)y * nx + x] = (T)(((double)v - base) * t.inv);
         }
         return inside ? v : (T)0;
     } else {
@@ -309,10 +310,10 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
     using Ops = IfOperands<T, MODE>;
     Ops q[P][RB];
     auto fetch = [&](Ops& o, int y) {
-        if_load<T, MODE>(o, in, terms, comp, zpl, x, y, nx, ny, nz, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
+        if_load<T, MODE>(o, in, terms, comp, zpl, x, y, nx, ny, nz, pbase, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
     };
     auto value = [&](const Ops& o, int y) -> T {
-        return if_value<T, MODE>(o, terms, comp, zpl, x, y, nx, ny, nz, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
+        return if_value<T, MODE>(o, terms, comp, zpl, x, y, nx, ny, nz, pbase, act && y >= 0 && y < ny, y >= y0 && y < y0 + S);
     };
 #pragma unroll
     for (int j = 0; j < P; ++j)
@@ -409,10 +410,10 @@ __global__ void __launch_bounds__(256) k_if_tile(IfTileArgs a0, const IfTileArgs
     auto inside = [&](int x, int y) { return x >= 0 && x < nx && y >= 0 && y < ny; };
     auto owned = [&](int x, int y) { return y >= y0 && y < y0 + tye && x >= x0 && x < x0 + txe; };
     auto fetch = [&](Ops& o, int x, int y) {
-        if_load<T, MODE>(o, in, terms, comp, z, x, y, nx, ny, nz, inside(x, y), owned(x, y));
+        if_load<T, MODE>(o, in, terms, comp, z, x, y, nx, ny, nz, pbase, inside(x, y), owned(x, y));
     };
     auto value = [&](const Ops& o, int x, int y) -> T {
-        return if_value<T, MODE>(o, terms, comp, z, x, y, nx, ny, nz, inside(x, y), owned(x, y));
+        return if_value<T, MODE>(o, terms, comp, z, x, y, nx, ny, nz, pbase, inside(x, y), owned(x, y));
     };
     // rows of the tile and its halo, one row per wave at a time; the columns beyond the first 64 (2R of them
     // at most) for several rows at once
