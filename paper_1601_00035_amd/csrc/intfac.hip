@@ -224,25 +224,37 @@ __device__ __forceinline__ void if_load(IfOperands<T, MODE>& o, const T* __restr
         }
     }
 }
+// The roundings are written out (fused multiply-adds by name, nothing contracted beside them): left to the
+// compiler, the product of a sum that is rounded first differs between the kernels and the loops that form a value,
+// and the walk, the tiles and the batched forms have to agree bit for bit.
 template <typename T, int MODE>
 __device__ __forceinline__ T if_value(const IfOperands<T, MODE>& o, const IfTerms& t, int comp, int z, int x, int y,
                                       int nx, int ny, int nz, long long pbase, bool inside, bool owned) {
+#pragma clang fp contract(off)
     if constexpr (MODE == IF_IN_COMB) {
-        double v = t.c0 * (double)o.v[0];
-        v += t.c1 * (double)o.v[1];
-        if (t.in2) v += t.c2 * (double)o.v[2];
+        double v = fma(t.c0, (double)o.v[0], t.c1 * (double)o.v[1]);
+        if (t.in2) v = fma(t.c2, (double)o.v[2], v);
         return inside ? (T)v : (T)0;
     } else if constexpr (MODE == IF_IN_PROJ) {
-        const T v = o.v[0] - (o.v[2] - o.v[1]) * (T)t.idx;
+        const T v = fma(-(o.v[2] - o.v[1]), (T)t.idx, o.v[0]);
         if (t.wnew && inside && owned) {
             double base = t.c_q * (double)o.v[3];
-            if (t.w1) base += t.c_w1 * (double)o.v[4];
+            if (t.w1) base = fma(t.c_w1, (double)o.v[4], base);
             ((T*)t.wnew)[pbase + (long long)y * nx + x] = (T)(((double)v - base) * t.inv);
         }
         return inside ? v : (T)0;
     } else {
         return o.v[0];
     }
+}
+
+// One output of a filter of fixed radius R from its 2R + 1 neighbours v(-R) .. v(R), weights wd(0) .. wd(R): from the
+// centre outwards, each step one rounding (written out for the same reason).
+template <int R, class W, class V> __device__ __forceinline__ double if_filter(const W& wd, const V& v) {
+    double acc = fma(wd(0), (double)v(0), wd(1) * (double)(v(-1) + v(1)));
+#pragma unroll
+    for (int d = 2; d <= R; ++d) acc = fma(wd(d), (double)(v(-d) + v(d)), acc);
+    return acc;
 }
 
 // Fused x and y passes (fixed radius R): a workgroup owns one (component, z) plane and S consecutive
@@ -342,10 +354,7 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
             T xf = (T)0;
             if (act) {
                 const T* p = &lt[i][R + x];
-                double acc = wd(0) * (double)p[0];
-#pragma unroll
-                for (int d = 1; d <= R; ++d) acc += wd(d) * (double)(p[-d] + p[d]);
-                xf = (T)acc;
+                xf = (T)if_filter<R>(wd, [&](int d) { return p[d]; });
             }
             win[2 * R + i] = xf;
         }
@@ -354,11 +363,7 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
             const int kk = ks * RB + i;  // rows ylo .. ylo + kk are in; the row y = ylo + kk - R is complete
             const int y = ylo + kk - R;
             if (kk >= 2 * R && act && y < ny && y < y0 + S) {
-                const T* v = win + i;
-                double acc = wd(0) * (double)v[R];
-#pragma unroll
-                for (int d = 1; d <= R; ++d) acc += wd(d) * (double)(v[R - d] + v[R + d]);
-                out[pbase + (long long)y * nx + x] = (T)acc;
+                out[pbase + (long long)y * nx + x] = (T)if_filter<R>(wd, [&](int d) { return win[i + R + d]; });
             }
         }
     }
@@ -368,7 +373,7 @@ __global__ void __launch_bounds__(256) k_if_xy(IfXyArgs a0, const IfXyArgs* __re
 // R points come into LDS at once (independent loads, one memory latency), the x filter runs in place over
 // the rows y0 - R .. y0 + ty + R - 1 (each thread 2 neighbouring outputs from R + 1 pair reads), the y
 // filter reads columns (each thread 8 outputs of one column).  Same operations and roundings as the
-// walking pass below, so the results are equal bit for bit.
+// walking pass above, so the results are equal bit for bit.
 struct IfTileArgs {
     const void* in;
     void* out;
@@ -415,6 +420,7 @@ __global__ void __launch_bounds__(256) k_if_tile(IfTileArgs a0, const IfTileArgs
     auto value = [&](const Ops& o, int x, int y) -> T {
         return if_value<T, MODE>(o, terms, comp, z, x, y, nx, ny, nz, pbase, inside(x, y), owned(x, y));
     };
+    auto wd = [&](int d) -> double { return A->wts.w[d]; };
     // rows of the tile and its halo, one row per wave at a time; the columns beyond the first 64 (2R of them
     // at most) for several rows at once
     const int nrows = tye + 2 * R, ncols = txe + 2 * R;
@@ -457,14 +463,8 @@ __global__ void __launch_bounds__(256) k_if_tile(IfTileArgs a0, const IfTileArgs
                 v[2 * k] = p.a;
                 v[2 * k + 1] = p.b;
             }
-            double s0 = A->wts.w[0] * (double)v[R], s1 = A->wts.w[0] * (double)v[R + 1];
-#pragma unroll
-            for (int d = 1; d <= R; ++d) {
-                s0 += A->wts.w[d] * (double)(v[R - d] + v[R + d]);
-                s1 += A->wts.w[d] * (double)(v[R + 1 - d] + v[R + 1 + d]);
-            }
-            f[i].a = (T)s0;
-            f[i].b = (T)s1;
+            f[i].a = (T)if_filter<R>(wd, [&](int d) { return v[R + d]; });
+            f[i].b = (T)if_filter<R>(wd, [&](int d) { return v[R + 1 + d]; });
         }
     }
     __syncthreads();
@@ -484,10 +484,8 @@ __global__ void __launch_bounds__(256) k_if_tile(IfTileArgs a0, const IfTileArgs
 #pragma unroll
         for (int k = 0; k < NY; ++k) {
             if (yr + k < tye) {
-                double acc = A->wts.w[0] * (double)v[k + R];
-#pragma unroll
-                for (int d = 1; d <= R; ++d) acc += A->wts.w[d] * (double)(v[k + R - d] + v[k + R + d]);
-                out[pbase + (long long)(y0 + yr + k) * nx + x0 + lane] = (T)acc;
+                out[pbase + (long long)(y0 + yr + k) * nx + x0 + lane] =
+                    (T)if_filter<R>(wd, [&](int d) { return v[k + R + d]; });
             }
         }
     }
@@ -549,9 +547,7 @@ __global__ void __launch_bounds__(256) k_if_strided(IfStrArgs a0, const IfStrArg
                 for (int d = R; d >= 1; --d) acc += wd(d) * (double)(v[m + R - d] + v[m + R + d]);
                 acc += wd(0) * (double)v[m + R];
             } else {
-                acc = wd(0) * (double)v[m + R];
-#pragma unroll
-                for (int d = 1; d <= R; ++d) acc += wd(d) * (double)(v[m + R - d] + v[m + R + d]);
+                acc = if_filter<R>(wd, [&](int d) { return v[m + R + d]; });
             }
             out[base + (long long)(k0 + m) * stride] = (T)acc;
         }
