@@ -198,11 +198,11 @@ int herk_check(nslgf_t h, const nslgf_state *st, int margin, double *div_max, vo
 
 /*
  * One IF-HERK step of each of n independent states (boxes of any supported sizes and dtypes, each
- * with its own u, d and work; none may share them).  The first call on a batch launches its passes, the
- * next one on the same states and step parameters captures them into a HIP graph (of batched passes, or of
- * per-problem branches, which are captured at once; see nslgf_set_batch_mode), and later calls replay the
- * graph, also after calls on other batches that were not captured.  Results equal n herk_step calls bit
- * for bit.
+ * with its own u, d and work; none may share them).  The first call on a batch launches its passes; if the
+ * next call is on the same states and step parameters, it captures them into a HIP graph (of batched passes, or
+ * of per-problem branches, which are captured at once; see nslgf_set_batch_mode), and later calls replay the
+ * graph, also with calls on other batches in between, until another batch is captured.  Results equal n
+ * herk_step calls bit for bit.
  * Advances every st->t by its dt.  Builds missing LGF spectra first (synchronising the stream).
  * Guarded states are checked inside the step and read back after it (one synchronisation); the call
  * returns NSLGF_ENONFINITE if any of them saw a non-finite value.

@@ -172,7 +172,7 @@ struct nslgf_ctx {
     int device = 0;
     nslgf::Profiler prof;
     std::unique_ptr<nslgf::BatchGraph> batch;
-    std::vector<unsigned long long> batch_key;  // the last batch launched without a graph
+    std::vector<unsigned long long> batch_key;  // the last batch stepped
     nslgf::BatchSlot batch_slots[4];
     int batch_slot = 0;
     int batch_groups = 0, batch_launches = 0;   // of the last batched call
@@ -1343,9 +1343,10 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
                                         (unsigned long long)st->guard, (unsigned long long)st->guard_margin};
         key.insert(key.end(), std::begin(k), std::end(k));
     }
-    // A batch met for the first time is launched pass by pass; met again right after, it is captured, and from
-    // then on replayed.  (Capturing costs 1.5 to 2.5 ms of host time in which the GPU has nothing to do: callers
-    // that alternate between batches, or build new ones, paid it every time.)
+    // A batch met for the first time is launched pass by pass; met again by the very next call, it is captured, and
+    // from then on replayed.  (Capturing costs 1.5 to 2.5 ms of host time in which the GPU has nothing to do: callers
+    // that alternate between batches, or build new ones, paid it every time.  A replay counts as a call too: of two
+    // batches that alternate, the one that was captured stays so.)
     bool launched = false;
     if ((!h->batch || h->batch->key != key) && h->batch_mode == NSLGF_BATCH_PASSES) {
         BatchPasses passes;
@@ -1353,12 +1354,12 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
         if (rc == NSLGF_OK) {
             NSLGF_TRY(ensure_branches(h, std::min((int)passes.groups.size(), 16)));
             if (h->batch_key == key) {
+                ProfScope ps(h, "batch_capture", s);
                 h->batch.reset();
                 NSLGF_TRY(capture_batch(h, passes, key));
             } else {
                 ProfScope ps(h, "batch_graph", s);
                 NSLGF_TRY(launch_batch(h, passes, s));
-                h->batch_key = key;
                 launched = true;
             }
         } else if (rc != NSLGF_ESTATE) {  // (NSLGF_ESTATE: a step has no batched form; captured per problem below)
@@ -1366,6 +1367,7 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
         }
     }
     if (!launched && (!h->batch || h->batch->key != key)) {
+        ProfScope ps(h, "batch_capture", s);
         h->batch.reset();
         const int nb = std::min(n, 16);
         NSLGF_TRY(ensure_branches(h, nb));
@@ -1417,6 +1419,7 @@ int herk_step_batched(nslgf_t h, nslgf_state* const* sts, int n, void* stream) {
         h->batch_groups = h->batch->groups;
         h->batch_launches = h->batch->launches;
     }
+    h->batch_key.swap(key);
     int rc = NSLGF_OK;
     for (int i = 0; i < n; ++i) {
         sts[i]->t += sts[i]->dt;
