@@ -201,7 +201,8 @@ int herk_check(nslgf_t h, const nslgf_state *st, int margin, double *div_max, vo
  * with its own u, d and work; none may share them).  The first call on a batch launches its passes; if the
  * next call is on the same states and step parameters, it captures them into a HIP graph (of batched passes, or
  * of per-problem branches, which are captured at once; see nslgf_set_batch_mode), and later calls replay the
- * graph, also with calls on other batches in between, until another batch is captured.  Results equal n
+ * graph, also with calls on other batches in between, until another batch is captured.  On a stream that the
+ * caller captures, a batch that has no graph yet is refused (NSLGF_ESTATE).  Results equal n
  * herk_step calls bit for bit.
  * Advances every st->t by its dt.  Builds missing LGF spectra first (synchronising the stream).
  * Guarded states are checked inside the step and read back after it (one synchronisation); the call

@@ -981,6 +981,13 @@ static int capture_batch(nslgf_ctx* h, const BatchPasses& b, const std::vector<u
 // Launches a recorded batch step on s without a graph.  Its tables go through one of four slots, each waited
 // for before it is used again.
 static int launch_batch(nslgf_ctx* h, const BatchPasses& b, hipStream_t s) {
+    // (a capture would record the upload from a slot that later calls write over)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        set_error("herk_step_batched: a batch that has no graph yet cannot be stepped on a capturing stream");
+        return NSLGF_ESTATE;
+    }
     BatchSlot& t = h->batch_slots[h->batch_slot];
     h->batch_slot = (h->batch_slot + 1) % 4;
     if (t.used) NSLGF_HIP_CHECK(hipEventSynchronize(t.done));

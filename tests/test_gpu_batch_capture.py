@@ -10,12 +10,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _states(sizes, seed):
+def _states(sizes, seed, dt=0.01):
     out = []
     for i, n in enumerate(sizes):
         g = torch.Generator().manual_seed(seed + i)
         u = (0.1 * torch.randn((3, n, n, n), generator=g, dtype=torch.float64)).to(DEV)
-        out.append(nslgf.HerkState(u, 0.1, 0.01, 300.0, "A", n_buf=2))
+        out.append(nslgf.HerkState(u, 0.1, dt, 300.0, "A", n_buf=2))
     return out
 
 
@@ -44,3 +44,32 @@ def test_captures_of_alternating_batches(order, captures):
         for x, y in zip(batched[k], single[k]):
             assert torch.equal(x.u, y.u) and torch.equal(x.d, y.d)
     assert count == captures
+
+
+def test_new_batch_is_refused_in_a_callers_capture():
+    """A batch without a graph of its own would put the upload of its argument table, from memory that later
+    calls write over, into the caller's graph.  It is refused; nothing is stepped, and the caller's capture and
+    the handle go on."""
+    a, ref = _states((16, 20), 1, 0.011), _states((16, 20), 1, 0.011)  # (a dt of their own: no graph serves them)
+    for st in _states((16, 20), 0):
+        st.step()  # (plans exist)
+    x = torch.zeros(4, device=DEV)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        with pytest.raises(nslgf.NslgfError) as e:
+            nslgf.herk_step_batched(a)
+        x.add_(1.0)
+    assert e.value.code == -5 and a[0].t == 0.0
+    graph.replay()
+    for i in range(6):  # (more calls than the handle has argument tables)
+        nslgf.herk_step_batched(a if i % 2 == 0 else _states((16, 20), 9 + i, 0.01 + 0.002 * i))
+        graph.replay()
+    for _ in range(3):
+        for st in ref:
+            st.step()
+    torch.cuda.synchronize()
+    assert x.tolist() == [7.0] * 4
+    for p, q in zip(a, ref):
+        assert torch.equal(p.u, q.u) and torch.equal(p.d, q.d)
