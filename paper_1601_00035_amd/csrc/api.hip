@@ -1488,24 +1488,31 @@ static int max_abs_host(nslgf_t h, const void* u, int nx, int ny, int nz, int n_
     return NSLGF_OK;
 }
 
-// Block weights of u into host memory: *mu, *nu point into the handle's result buffer (synchronised; valid
-// until its next use).
+// Block weights of u into the caller's host memory (synchronised).  The kernel writes them straight to the handle's
+// pinned result buffer, which saves a copy's launch, where they take at most kPinnedResults there; beyond, which
+// is blocks of a few cells on a large box (268 MB at 256^3 with blocks of one cell), they go through device memory.
+constexpr size_t kPinnedResults = 4u << 20;
 static int block_weights_host(nslgf_t h, int dtype, const void* u, int nx, int ny, int nz, int nb, int n_buf, double dx,
-                              const double** mu, const double** nu, hipStream_t s) {
+                              double* mu, double* nu, hipStream_t s) {
     const long long n = (long long)ceil_div(nx, nb) * ceil_div(ny, nb) * ceil_div(nz, nb);
-    NSLGF_TRY(h->results.ensure((size_t)2 * n * sizeof(double)));
-    double* host = (double*)h->results.p;
-    double* d = host;
-    const bool direct = nb <= 16;  // (larger blocks meet in atomics, which need device memory)
-    if (!direct) {
-        NSLGF_TRY(h->partial.ensure((size_t)2 * n * sizeof(double)));
-        d = (double*)h->partial.p;
-    }
+    const size_t bytes = (size_t)n * sizeof(double);
+    const bool pinned = 2 * bytes <= kPinnedResults;
+    if (pinned) NSLGF_TRY(h->results.ensure(2 * bytes));
+    const bool direct = pinned && nb <= 16;  // (larger blocks meet in atomics, which need device memory)
+    if (!direct) NSLGF_TRY(h->partial.ensure(2 * bytes));
+    double* const host = (double*)h->results.p;
+    double* const d = direct ? host : (double*)h->partial.p;
     NSLGF_PROF(h, "block_weights", s, launch_block_weights(dtype, u, nx, ny, nz, nb, n_buf, dx, d, d + n, s));
-    if (!direct) NSLGF_HIP_CHECK(hipMemcpyAsync(host, d, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s));
+    if (!pinned) {
+        NSLGF_HIP_CHECK(hipMemcpyAsync(mu, d, bytes, hipMemcpyDeviceToHost, s));
+        NSLGF_HIP_CHECK(hipMemcpyAsync(nu, d + n, bytes, hipMemcpyDeviceToHost, s));
+        NSLGF_HIP_CHECK(hipStreamSynchronize(s));
+        return NSLGF_OK;
+    }
+    if (!direct) NSLGF_HIP_CHECK(hipMemcpyAsync(host, d, 2 * bytes, hipMemcpyDeviceToHost, s));
     NSLGF_HIP_CHECK(hipStreamSynchronize(s));
-    *mu = host;
-    *nu = host + n;
+    std::memcpy(mu, host, bytes);
+    std::memcpy(nu, host + n, bytes);
     return NSLGF_OK;
 }
 
@@ -1641,12 +1648,7 @@ int block_weights(nslgf_t h, const void* u, int nx, int ny, int nz, int nb, int 
     NSLGF_CHECK_ARG(n_buf >= 0, "block_weights: n_buf must be >= 0");
     NSLGF_CHECK_ARG(std::isfinite(dx) && dx > 0, "block_weights: dx must be > 0");
     hipStream_t s = (hipStream_t)stream;
-    const double *m, *v;
-    NSLGF_TRY(block_weights_host(h, dtype, u, nx, ny, nz, nb, n_buf, dx, &m, &v, s));
-    const size_t bytes = (size_t)ceil_div(nx, nb) * ceil_div(ny, nb) * ceil_div(nz, nb) * sizeof(double);
-    std::memcpy(mu, m, bytes);
-    std::memcpy(nu, v, bytes);
-    return NSLGF_OK;
+    return block_weights_host(h, dtype, u, nx, ny, nz, nb, n_buf, dx, mu, nu, s);
 }
 
 int classify_blocks(const double* mu, const double* nu, int bx, int by, int bz, double eps_supp, double eps_soln,
@@ -1686,6 +1688,7 @@ int herk_run_adaptive(nslgf_t h, nslgf_state* st, int nsteps, int block, double 
     NSLGF_TRY(h->blockmask.ensure((size_t)2 * nbk));
     unsigned char* dsupp = (unsigned char*)h->blockmask.p;
     unsigned char* dsoln = dsupp + nbk;
+    std::vector<double> mu(nbk), nu(nbk);
     std::vector<unsigned char> supp(nbk), soln(nbk), xsoln(nbk), psupp, psoln;
     const StateLayout L = state_layout(nx, ny, nz);
     const size_t es = dtype_size(dt_);
@@ -1706,10 +1709,9 @@ int herk_run_adaptive(nslgf_t h, nslgf_state* st, int nsteps, int block, double 
     } restore{st, st->supp_blocks, st->soln_blocks, st->block};
     for (int step = 0; step < nsteps; ++step) {
         // the domain of this step from the block weights of u (Sec. 4.3)
-        const double *mu, *nu;
-        NSLGF_TRY(block_weights_host(h, dt_, st->u, nx, ny, nz, block, st->n_buf, st->dx, &mu, &nu, s));
-        classify_blocks_host(mu, nu, bx, by, bz, eps_supp, eps_soln, n_xb, nullptr, supp.data(), soln.data(),
-                             xsoln.data());
+        NSLGF_TRY(block_weights_host(h, dt_, st->u, nx, ny, nz, block, st->n_buf, st->dx, mu.data(), nu.data(), s));
+        classify_blocks_host(mu.data(), nu.data(), bx, by, bz, eps_supp, eps_soln, n_xb, nullptr, supp.data(),
+                             soln.data(), xsoln.data());
         bool edge = false;
         for (int k = 0; k < bz && !edge; ++k)
             for (int j = 0; j < by && !edge; ++j)
@@ -1784,10 +1786,10 @@ int herk_run_active(nslgf_t h, nslgf_state* st, int nsteps, int block, double ep
         const long long nbk = (long long)bb[0] * bb[1] * bb[2];
         // classification on the current box (block weights of its velocity, Sec. 4.3)
         void* U = h->act_u[cur].p;
-        const double *mu, *nu;
-        NSLGF_TRY(block_weights_host(h, dt_, U, bn[0], bn[1], bn[2], block, st->n_buf, st->dx, &mu, &nu, s));
+        std::vector<double> mu(nbk), nu(nbk);
+        NSLGF_TRY(block_weights_host(h, dt_, U, bn[0], bn[1], bn[2], block, st->n_buf, st->dx, mu.data(), nu.data(), s));
         std::vector<unsigned char> supp(nbk), soln(nbk), xs(nbk);
-        classify_blocks_host(mu, nu, bb[0], bb[1], bb[2], eps_supp, eps_soln, 0, nullptr, supp.data(),
+        classify_blocks_host(mu.data(), nu.data(), bb[0], bb[1], bb[2], eps_supp, eps_soln, 0, nullptr, supp.data(),
                              soln.data(), xs.data());
         // D_supp, D_soln (united with D_supp) in the block coordinates of G, then D_xsoln and its bounding box
         std::fill(gs.begin(), gs.end(), 0);
