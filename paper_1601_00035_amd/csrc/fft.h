@@ -6,9 +6,7 @@
 // butterflies j = t + b * TP (b < E / R) of thread t: it reads x[j + r L/R], r < R, twiddles them by
 // W_{NS R}^{r (j mod NS)}, applies the length-R DFT and writes the outputs to
 // (j div NS) NS R + (j mod NS) + r NS.  Outputs of the last pass therefore sit at j + r L/R_last in
-// natural order, which is also the input layout of a following transform whose first radix is
-// R_last (used to fuse forward transform, spectral multiply and inverse transform without an
-// exchange).  Forward transforms use e^{-2 pi i jk/L}; inverse ones e^{+2 pi i jk/L}; neither scales.
+// natural order.  Forward transforms use e^{-2 pi i jk/L}; inverse ones e^{+2 pi i jk/L}; neither scales.
 #pragma once
 
 #include "common.h"
@@ -165,10 +163,11 @@ template <typename T, bool INV> struct DFT<T, 6, INV> {
     }
 };
 
-// Pruned butterflies of the zero-padded transforms.  DFTHalfIn: inputs R/2 .. R-1 are zero (the
+// Pruned butterflies of the zero-padded column transforms.  DFTHalfIn: inputs R/2 .. R-1 are zero (the
 // first pass of a transform whose upper half is padding).  DFTHalfOut: only outputs 0 .. R/2-1 are
-// kept (the last pass of a transform whose upper half is discarded).  Even radices 2, 4, 8; the
+// kept (the last pass of a transform whose upper half is discarded).  Radices 2, 4 and 8 (`prunable`); the
 // kept values equal the full butterfly's.
+template <int R> __host__ __device__ constexpr bool prunable() { return R == 2 || R == 4 || R == 8; }
 template <typename T, int R, bool INV> struct DFTHalfIn;
 template <typename T, bool INV> struct DFTHalfIn<T, 2, INV> {
     __device__ __forceinline__ static void run(cplx<T>* v) { v[1] = v[0]; }
@@ -218,11 +217,7 @@ template <typename T, bool INV> struct DFTHalfOut<T, 8, INV> {
 
 // ---- passes -----------------------------------------------------------------------------------
 // tw: root table tw[m] = exp(-2 pi i m / L), m < L (forward); the inverse conjugates it.
-// PRUNE bit 1: this is the first pass and inputs r >= R/2 of every butterfly are zero; bit 2: this is
-// the last pass and only outputs r < R/2 are used.  Only even radices 2, 4, 8 are pruned.
-template <int R> __host__ __device__ constexpr bool prunable() { return R == 2 || R == 4 || R == 8; }
-
-template <typename T, int L, int E, int TP, bool INV, int NS, int R, int PRUNE = 0>
+template <typename T, int L, int E, int TP, bool INV, int NS, int R>
 __device__ __forceinline__ void pass_compute(cplx<T>* v, int t, const cplx<T>* __restrict__ tw) {
 #pragma unroll
     for (int b = 0; b < E / R; ++b) {
@@ -235,13 +230,7 @@ __device__ __forceinline__ void pass_compute(cplx<T>* v, int t, const cplx<T>* _
                 v[b * R + r] = INV ? cmulc<T>(v[b * R + r], w) : cmul<T>(v[b * R + r], w);
             }
         }
-        if constexpr ((PRUNE & 1) && prunable<R>()) {
-            DFTHalfIn<T, R, INV>::run(v + b * R);
-        } else if constexpr ((PRUNE & 2) && prunable<R>()) {
-            DFTHalfOut<T, R, INV>::run(v + b * R);
-        } else {
-            DFT<T, R, INV>::run(v + b * R);
-        }
+        DFT<T, R, INV>::run(v + b * R);
     }
 }
 
@@ -274,40 +263,35 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 // (The TP threads of a transform are lanes of one wave, so its exchanges need no workgroup barrier.)
-template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, class RL> struct Runner;
+template <typename T, int L, int E, int TP, bool INV, int NS, class RL> struct Runner;
 
-template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, int R>
-struct Runner<T, L, E, TP, INV, NS, PRUNE, RList<R>> {
+template <typename T, int L, int E, int TP, bool INV, int NS, int R>
+struct Runner<T, L, E, TP, INV, NS, RList<R>> {
     template <class Acc>
     __device__ __forceinline__ static void run(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc&) {
-        // a single-pass transform prunes only one side (input pruning wins)
-        constexpr int P1 = (NS == 1 && (PRUNE & 1)) ? 1 : (PRUNE & 2);
-        pass_compute<T, L, E, TP, INV, NS, R, P1>(v, t, tw);
+        pass_compute<T, L, E, TP, INV, NS, R>(v, t, tw);
     }
 };
 
-template <typename T, int L, int E, int TP, bool INV, int NS, int PRUNE, int R, int R2, int... Rest>
-struct Runner<T, L, E, TP, INV, NS, PRUNE, RList<R, R2, Rest...>> {
+template <typename T, int L, int E, int TP, bool INV, int NS, int R, int R2, int... Rest>
+struct Runner<T, L, E, TP, INV, NS, RList<R, R2, Rest...>> {
     template <class Acc>
     __device__ __forceinline__ static void run(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc& acc) {
         static_assert(64 % TP == 0, "a transform's threads must be lanes of one wave");
-        pass_compute<T, L, E, TP, INV, NS, R, (NS == 1) ? (PRUNE & 1) : 0>(v, t, tw);
+        pass_compute<T, L, E, TP, INV, NS, R>(v, t, tw);
         wave_sync();
         pass_store<T, L, E, TP, NS, R>(v, t, acc);
         wave_sync();
         pass_load<T, L, E, TP, R2>(v, t, acc);
-        Runner<T, L, E, TP, INV, NS * R, PRUNE, RList<R2, Rest...>>::run(v, t, tw, acc);
+        Runner<T, L, E, TP, INV, NS * R, RList<R2, Rest...>>::run(v, t, tw, acc);
     }
 };
 
 // Full transform on registers: input v[b R1 + r] = x[t + b TP + r L/R1] (R1 = first radix of the
-// list), output v[b Rl + r] = X[t + b TP + r L/Rl] (Rl = last radix).  PRUNE bit 1: the inputs
-// x[L/2 .. L-1] are zero (the caller leaves v[b R1 + r], r >= R1/2, unset or zero); bit 2: only
-// X[0 .. L/2-1] are wanted (v[b Rl + r], r >= Rl/2, are left undefined).  Either applies only when the
-// first (bit 1) or last (bit 2) radix is 2, 4 or 8.
-template <typename T, int L, bool INV, class RL, class Acc, int E = Plan1D<L>::E, int PRUNE = 0>
+// list), output v[b Rl + r] = X[t + b TP + r L/Rl] (Rl = last radix).
+template <typename T, int L, bool INV, class RL, class Acc, int E = Plan1D<L>::E>
 __device__ __forceinline__ void fft_regs(cplx<T>* v, int t, const cplx<T>* __restrict__ tw, Acc& acc) {
-    Runner<T, L, E, L / E, INV, 1, PRUNE, RL>::run(v, t, tw, acc);
+    Runner<T, L, E, L / E, INV, 1, RL>::run(v, t, tw, acc);
 }
 
 // LDS accessor of the row kernels: one contiguous segment per row, one pad element every 2^S

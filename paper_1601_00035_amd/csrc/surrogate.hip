@@ -44,10 +44,6 @@ __device__ __forceinline__ bf16x8 pack8(const bf16_t v[8]) {
     return __builtin_bit_cast(bf16x8, q);
 }
 
-__device__ __forceinline__ int tap_dz(int t) { return t / 9 - 1; }
-__device__ __forceinline__ int tap_dy(int t) { return (t / 3) % 3 - 1; }
-__device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
-
 // Y[v][n] = act(sum_tap sum_k X[v + SIGN off(tap)][k] Wn[tap][n][k]);  K % 16 == 0, N % 32 == 0.
 // A workgroup of 9 wavefronts owns one 32 x 32 output tile; wave g sums the three dx taps of one (dz, dy) pair
 // with its A rows gathered from the activation, and the nine partial tiles are added in LDS in a fixed order.
