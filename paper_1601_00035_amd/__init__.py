@@ -377,7 +377,7 @@ def tuning_load(path: str, device: int | None = None):
 
 
 def plan_info(nx: int, ny: int, nz: int, dtype=torch.float64, device: int | None = None) -> tuple:
-    """(y variant, z variant) of the convolution plan for this box and dtype (built if needed)."""
+    """(y, z) plan numbers of the convolution plan for this box and dtype (built if needed)."""
     vy, vz = ctypes.c_int(), ctypes.c_int()
     code = F64 if dtype == torch.float64 else F32
     dev = torch.cuda.current_device() if device is None else device

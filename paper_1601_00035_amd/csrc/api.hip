@@ -188,7 +188,7 @@ struct nslgf_ctx {
     int batch_mode = NSLGF_BATCH_PASSES;
     bool no_alloc = false;   // inside lgf_convolve_noalloc: lookups that would allocate fail instead
     void* scratch = nullptr; // this device's address of the library's fixed scratch array
-    int fft_plan = -1;  // column-pass plan choice: -1 per-dtype default, -2 autotune, else a number 0..2
+    int fft_plan = -1;  // column-pass plan choice: -1 per-dtype default, -2 the same, else a number 0..2
     int tune_mode = NSLGF_TUNE_DEFAULT;
     // launch shapes per (nx, ny, nz, dtype): tuned on first use in NSLGF_TUNE_AUTO, or loaded from a file
     std::map<std::tuple<int, int, int, int>, nslgf::TuneEntry> tunings;
@@ -2148,7 +2148,7 @@ int nslgf_tuning_load(nslgf_t h, const char* path) {
         e.vz = vz;
         read.emplace_back(std::make_tuple(nx, ny, nz, dt), e);
     }
-    // plans built before under the default choice are rebuilt with the loaded variants on next use
+    // plans built before under the default choice are rebuilt with the loaded numbers on next use
     for (const auto& kv : read) {
         h->tunings[kv.first] = kv.second;
         h->plans.erase(std::tuple_cat(kv.first, std::make_tuple(-1)));

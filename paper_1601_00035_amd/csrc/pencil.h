@@ -14,13 +14,14 @@
 // read them, so a whole forward, multiply, inverse takes two barriers (eight when every exchange left the
 // wave).
 //
-// What bounds it: the 256^3 passes run at 4.3 to 5.3 TB/s of their algorithmic bytes, the rate of a large
-// copy (5.2), so memory; the boxes that stay in the last-level cache are bound by LDS and issue.  Before
-// (Stockham passes whose every exchange crossed the workgroup; lengths 320 and 384 in five passes through
-// half-size LDS tiles) and now, fused z pass, us per launch of one / three components: FP64 256^3 350 / 928
-// -> 310 / 830, 192^3 177 / 492 -> 138 / 387, 160^3 110 / 294 -> 81 / 232; FP32 256^3 203 / 563 -> 165 /
-// 458, 192^3 113 / 325 -> 72 / 207, 160^3 63 / 166 -> 42 / 128.  (At 256^3 in FP64 the y inverse then takes
-// 170 to 190 us instead of 150: it waits for the z pass's writes to drain, and the pair is HBM-bound.)
+// What bounds it: the y passes run at 4.7 to 5.2 TB/s of their algorithmic bytes at 256^3, the rate of a large
+// copy (5.2), so memory; the fused z pass at 3.7 to 3.9 in FP64 and 3.4 in FP32, memory and, since a workgroup
+// waits for all of its loads before it starts, their latency; the boxes that stay in the last-level cache are
+// bound by LDS and issue.  Before (Stockham passes whose every exchange crossed the workgroup; lengths 320 and
+// 384 in five passes through half-size LDS tiles) and now, fused z pass within a solve, us per launch of one /
+// three components: FP64 256^3 359 / 975 -> 328 / 878, 192^3 196 / 554 -> 151 / 432, 160^3 115 / 323 -> 87 / 256;
+// FP32 256^3 222 / 602 -> 176 / 501, 192^3 127 / 375 -> 75 / 239, 160^3 66 / 193 -> 44 / 137.  (At 256^3 in FP64
+// the y inverse then takes 160 / 472 us instead of 153 / 455: it waits for the z pass's writes to drain.)
 // Measured and left out: one resident grid that loads its next tile ahead (the compiler keeps the twiddles
 // in registers and spills: 300 -> 665 us at 512; no gain where it does not spill), and column chunks small
 // enough for the last-level cache (no faster: each chunk's launches are too small).
@@ -187,7 +188,8 @@ k_pencil(ColPass a0, const ColPass* __restrict__ da, int per) {
             }
         }
     }
-    // the twiddles reach LDS while the data loads are still under way
+    // (the pointers come from the arguments or from the batch's table, which the compiler addresses generically; such
+    // loads count with the LDS operations too, so these writes wait for the data and the spectrum)
 #pragma unroll
     for (int i = 0; i < NT2; ++i)
         if (tid + i * 64 * NW < NTW2) tw2[tid + i * 64 * NW] = t2[i];

@@ -3,7 +3,8 @@
 // The 3x3x3 convolutions are implicit GEMMs on v_mfma_f32_32x32x16_bf16 (BF16 operands, FP32
 // accumulation), 16 input channels a step: the A operand is the channels-last activation (the 8 BF16
 // values a lane supplies are contiguous channels of one voxel), through an LDS halo or straight from
-// memory on small volumes, the B operand the weight rows.  Operand layout of the instruction (wave64), checked by sur_mfma_selftest:
+// memory on small volumes, the B operand the weight rows.  Operand layout of the instruction (wave64),
+// checked by sur_mfma_selftest:
 //   A (32 x 16): lane l supplies A[l % 32][8 (l / 32) + j], j < 8
 //   B (16 x 32): lane l supplies B[8 (l / 32) + j][l % 32]
 //   D (32 x 32): lane l holds D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32] in accumulator i < 16
@@ -51,7 +52,8 @@ __device__ __forceinline__ bf16x8 pack8(const bf16_t v[8]) {
 // steps is the time: one wave per tile over all 27 taps took 28 us forward and 51 us for the data gradient at
 // 16^3, 96 -> 128 channels, and 27 and 48 us at 8^3; this takes 15 and 22, and 8 and 14.  MT = 2 gives a
 // workgroup two tiles of voxels, which halves its weight reads (19 and 27 us with one at 16^3); below 256
-// tiles that leaves CUs idle (12^3: 10.1 and 14.9 us with one, 10.8 and 20.9 with two).
+// tiles that leaves CUs idle (12^3: 10.1 and 14.9 us with one, 10.8 and 20.9 with two).  Its six row pointers take it
+// past its 96 registers: 8 spill.
 __device__ __forceinline__ int split_row(int i, int half) { return 8 * (i / 4) + 4 * half + (i % 4); }
 template <bool RELU, int SIGN, int MT>
 __global__ void __launch_bounds__(576, MT == 1 ? 7 : 5) k_conv_split(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wn,
@@ -126,11 +128,11 @@ __global__ void __launch_bounds__(576, MT == 1 ? 7 : 5) k_conv_split(const bf16_
 // and not stored.  The sum runs over slices, then dy, dx, dz (+1 first) in a fixed order:
 // results are deterministic (dx before dy: 122 us at 128^3, 16 -> 32 channels, this 108).
 // The time is the matrix operations and the latency of a slice's staging and of the weights, which the three
-// workgroups of a CU overlap (128^3, 32 -> 32 channels: 183 to 194 us, 590 to 635 TFLOP/s; a form with the
-// weights in LDS and the next slice in registers ran two workgroups a CU and took 277).  Rows along y served
-// three dy taps before, which tied the block to 32 voxels along x: widths that 32 does not divide went through
-// the gathering kernel (112^3, 32 -> 32: 328 us, now 123; 56^3, 32 -> 64: 81 and 153 for the data gradient,
-// now 39 and 50; 80^3: 121, now 47).
+// workgroups of a CU overlap (128^3, 32 -> 32 channels: 183 to 194 us back to back, 590 to 635 TFLOP/s, and 153 to
+// 166 between other passes, at a higher clock; a form with the weights in LDS and the next slice in registers ran
+// two workgroups a CU and took 277).  Rows along y served three dy taps before, which tied the block to 32 voxels
+// along x: widths that 32 does not divide went through the gathering kernel (112^3, 32 -> 32: 328 us, now 123;
+// 56^3, 32 -> 64: 81 and 153 for the data gradient, now 39 and 50; 80^3: 121, now 47).
 constexpr int kLdsZ = 4;  // z planes of a workgroup
 template <int TX> struct LdsBlk {
     static constexpr int TY = 32 / TX, BY = 4 * TY, HX = TX + 2, HY = BY + 2, HZ = kLdsZ + 2;
@@ -386,12 +388,13 @@ __global__ void __launch_bounds__(256) k_cast_ex(const float* __restrict__ src, 
 // row, so that the voxel before and after a group (dx = -1 and +1) come from groups that it holds.
 // PAD: rows of W voxels, W % 8 != 0, filled up with zeros; the one product that would pair such a filler with a
 // voxel of the volume is masked, as are the groups that a half-wave lacks (an infinity there must not count).
-// One workgroup a CU (its LDS, and waves of about 160 registers; the tenth only loads); the time is the matrix
-// operations, 3 of the 9 waves on one SIMD, and a step's LDS latency.  The form before had every wave load its
-// own operands and was bound by L2 (each XCD read all of both tensors for several of the nine pairs): 128^3,
-// 32 -> 32: 276 us with the sums, now 174; 64^3, 32 -> 64: 79, now 63; 112^3: 223, now 144; 56^3, 32 -> 64: 192,
-// now 55; rows that 8 does not divide, gathered voxel by voxel: 12^3, 96 -> 128: 193, now 28.  One row a step: 10 us
-// more at 128^3; two workgroups a CU at 96 registers spilled and took 650.
+// One workgroup a CU (its LDS, and waves of 140 to 168 registers, of which 4, padded 1, spill at eight groups a
+// segment; the tenth wave only loads); the time is the matrix operations, 3 of the 9 waves on one SIMD, and a
+// step's LDS latency.  The form before had every wave load its own operands and was bound by L2 (each XCD read all
+// of both tensors for several of the nine pairs): 128^3, 32 -> 32: 276 us with the sums, now 174; 64^3, 32 -> 64:
+// 79, now 63; 112^3: 223, now 144; 56^3, 32 -> 64: 192, now 55; rows that 8 does not divide, gathered voxel by
+// voxel: 12^3, 96 -> 128: 193, now 28.  One row a step: 10 us more at 128^3; two workgroups a CU at 96 registers
+// spilled and took 650.
 constexpr int kWgThreads = 640;
 struct WgradPlan {
     int nx, S, segs, SH, RS;  // groups of a row and of a segment, segments, groups of a half-wave, rows of a step
