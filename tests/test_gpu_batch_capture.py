@@ -25,7 +25,8 @@ def test_captures_of_alternating_batches(order, captures):
     sizes = {"a": (16, 20), "b": (24,)}
     batched = {k: _states(v, ord(k)) for k, v in sizes.items()}
     single = {k: _states(v, ord(k)) for k, v in sizes.items()}
-    nslgf.herk_step_batched(_states((12,), 7))  # (nothing of what follows was stepped last)
+    nslgf.set_batch_mode(nslgf.BATCH_PER_PROBLEM)  # (drops the graph that an earlier batch left, whose states may
+    nslgf.set_batch_mode(nslgf.BATCH_PASSES)       # have had these ones' memory and parameters)
     for k in "ab":
         for st in _states(sizes[k], 0):
             st.step()  # (plans exist)
