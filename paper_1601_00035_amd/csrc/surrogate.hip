@@ -320,57 +320,82 @@ __global__ void __launch_bounds__(256) k_rows_to_blocked8(const bf16_t* __restri
 
 // FP32 -> BF16 cast of channels-last [nvox][C] with an optional ReLU backward and an optional blocked
 // copy: val = src (0 where act is given and not > 0, as k_relu_bwd leaves it), y[v][c] = bf16(val) and
-// yb[v / 8][c][v % 8] = bf16(val) (the layout of k_to_blocked8).  A workgroup takes 128 voxels x 32 channels; a
-// thread two times two voxels x 4 channels, so that eight lanes read a whole 128-byte row; the blocked copy goes
-// through LDS and is written in rows of 16-byte words.  Bytes bound it (one thread per 8 voxels x 8 channels,
-// which touched every line several times: at 128^3 x 32 channels 142 us, now 92, 5.9 TB/s; with act 198, now 165).
-__global__ void __launch_bounds__(256) k_cast_ex(const float* __restrict__ src, const float* __restrict__ act,
-                                                 bf16_t* __restrict__ y, bf16_t* __restrict__ yb, long long nvox, int C,
-                                                 int chunks) {
-    __shared__ unsigned tile[16][32][4 + 1];  // [group][channel][pairs of voxels], one word of padding
+// yb[v / 8][c][v % 8] = bf16(val) (the layout of k_to_blocked8).
+__device__ __forceinline__ uint2 cast4(float4 s, const float4* a) {
+    if (a) {
+        if (!(a->x > 0.f)) s.x = 0.f;
+        if (!(a->y > 0.f)) s.y = 0.f;
+        if (!(a->z > 0.f)) s.z = 0.f;
+        if (!(a->w > 0.f)) s.w = 0.f;
+    }
+    return make_uint2(f2bf(s.x) | (unsigned)f2bf(s.y) << 16, f2bf(s.z) | (unsigned)f2bf(s.w) << 16);
+}
+// Without the blocked copy the layout does not matter: a workgroup takes 2048 values in a row (us at 128^3, in the
+// tiles below and so: 32 channels 70 and 67, 48 channels 195 and 99, 64 channels 167 and 131; with act 122 and
+// 117, 303 and 174, 295 and 239).
+template <bool ACT>
+__global__ void __launch_bounds__(256) k_cast_flat(const float4* __restrict__ src, const float4* __restrict__ act,
+                                                   uint2* __restrict__ y, long long n4) {
+    const long long e0 = (long long)blockIdx.x * 512 + threadIdx.x;
+    float4 s[2], a[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const long long e = min(e0 + 256 * i, n4 - 1);
+        s[i] = src[e];
+        if (ACT) a[i] = act[e];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (e0 + 256 * i < n4) y[e0 + 256 * i] = cast4(s[i], ACT ? &a[i] : nullptr);
+}
+// With it a workgroup takes 4096 / CW voxels x CW channels; a thread two times two voxels x 4 channels, so that
+// CW / 4 lanes read 128 or 256 bytes of a row; the blocked copy goes through LDS and is written in rows of
+// 16-byte words.  Bytes bound it (one thread per 8 voxels x 8 channels, which touched every line several times: at
+// 128^3 x 32 channels 142 us, now 92, 5.9 TB/s; with act 198, now 165).
+template <int CW>
+__global__ void __launch_bounds__(256) k_cast_blocked(const float* __restrict__ src, const float* __restrict__ act,
+                                                      bf16_t* __restrict__ y, bf16_t* __restrict__ yb, long long nvox,
+                                                      int C, int chunks) {
+    constexpr int VT = 4096 / CW, LR = CW / 4, NP = 256 / LR;  // voxels; lanes of a row; pairs of voxels at a time
+    __shared__ unsigned tile[VT / 8][CW][4 + 1];  // [group][channel][pairs of voxels], one word of padding
     const int tid = threadIdx.x;
-    const long long v0 = (long long)(blockIdx.x / chunks) * 128;
-    const int c0 = (int)(blockIdx.x % chunks) * 32;
-    const int cq = (tid % 8) * 4, c = c0 + cq;
+    // the chunks of one row on one XCD (workgroup b runs on XCD b mod 8)
+    const int run = 8 * chunks, first = (int)blockIdx.x / run * run, r = (int)blockIdx.x - first;
+    const int lg = first + run <= (int)gridDim.x ? first + r % 8 * chunks + r / 8 : (int)blockIdx.x;
+    const long long v0 = (long long)(lg / chunks) * VT;
+    const int c0 = lg % chunks * CW;
+    const int cq = (tid % LR) * 4, c = c0 + cq;
     float4 s[2][2], a[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const long long v = v0 + 64 * i + tid / 8 * 2 + j;
+            const long long v = v0 + 2 * NP * i + tid / LR * 2 + j;
             const bool ok = v < nvox && c < C;
             s[i][j] = ok ? *(const float4*)(src + v * C + c) : make_float4(0.f, 0.f, 0.f, 0.f);
             if (act) a[i][j] = ok ? *(const float4*)(act + v * C + c) : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int p = 32 * i + tid / 8;  // the pair of voxels
-        unsigned w[2][4];
+        const int p = NP * i + tid / LR;  // the pair of voxels
+        uint2 w[2];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            float q[4] = {s[i][j].x, s[i][j].y, s[i][j].z, s[i][j].w};
-            if (act) {
-                if (!(a[i][j].x > 0.f)) q[0] = 0.f;
-                if (!(a[i][j].y > 0.f)) q[1] = 0.f;
-                if (!(a[i][j].z > 0.f)) q[2] = 0.f;
-                if (!(a[i][j].w > 0.f)) q[3] = 0.f;
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) w[j][k] = f2bf(q[k]);
+            w[j] = cast4(s[i][j], act ? &a[i][j] : nullptr);
             const long long v = v0 + 2 * p + j;
-            if (v < nvox && c < C) *(uint2*)(y + v * C + c) = make_uint2(w[j][0] | w[j][1] << 16, w[j][2] | w[j][3] << 16);
+            if (v < nvox && c < C) *(uint2*)(y + v * C + c) = w[j];
         }
-        if (yb) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) tile[p / 4][cq + k][p % 4] = w[0][k] | w[1][k] << 16;
-        }
+        unsigned* t = &tile[p / 4][cq][p % 4];
+        t[0] = (w[0].x & 0xffffu) | w[1].x << 16;
+        t[5] = w[0].x >> 16 | (w[1].x & 0xffff0000u);
+        t[10] = (w[0].y & 0xffffu) | w[1].y << 16;
+        t[15] = w[0].y >> 16 | (w[1].y & 0xffff0000u);
     }
-    if (!yb) return;
     __syncthreads();
-    const int nc = min(32, C - c0);
+    const int nc = min(CW, C - c0);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int e = tid + 256 * i, g = e / 32, ch = e % 32;
+        const int e = tid + 256 * i, g = e / CW, ch = e % CW;
         if (v0 + 8 * g < nvox && ch < nc) {
             const unsigned* t = tile[g][ch];
             *(uint4*)(yb + ((v0 / 8 + g) * C + c0 + ch) * 8) = make_uint4(t[0], t[1], t[2], t[3]);
@@ -620,7 +645,7 @@ __device__ __forceinline__ long long coarse_of(long long v, int D, int H, int W)
 
 // Fused resampling, skip sum and cast: val[v][c] = scale * coarse[parent(v)][c] + skip[v][c], parent(v)
 // the voxel of the half-resolution grid that holds v (scale 1: the nearest-neighbour upsampling; scale
-// 1/8: the adjoint of the 2x2x2 average pooling), then as k_cast_ex: zero where act is given and not
+// 1/8: the adjoint of the 2x2x2 average pooling), then as k_cast_blocked: zero where act is given and not
 // > 0, y[v][c] = bf16(val), and yb[v / 8][c][v % 8] = bf16(val) when yb is given.  The product and the
 // sum are rounded one at a time, as the separate passes round them.  One thread: 8 voxels x 8 channels.
 __global__ void __launch_bounds__(256) k_cast_up(const float* __restrict__ coarse, float scale,
@@ -771,7 +796,7 @@ __global__ void __launch_bounds__(256) k_mse(const float* __restrict__ pred, con
 
 // Squared error with the gradient written only as its BF16 copy y[v][c] and, when yb is given, the
 // blocked copy yb[v / 8][c][v % 8] (the layout of k_to_blocked8): the gradient values are those of
-// k_mse, rounded as k_cast_ex rounds them.  One thread: 8 voxels x 8 channels (grid-stride); per-block
+// k_mse, rounded as sur_cast_bf16_ex rounds them.  One thread: 8 voxels x 8 channels (grid-stride); per-block
 // FP64 partial sums of the squared error, in the order of this decomposition.
 __global__ void __launch_bounds__(256) k_mse_cast(const float* __restrict__ pred, const float* __restrict__ tgt,
                                                   bf16_t* __restrict__ y, bf16_t* __restrict__ yb,
@@ -1090,8 +1115,23 @@ int sur_cast_bf16_ex(nslgf_t h, const void* src, const void* act, void* y, void*
                     "sur_cast_bf16_ex: need src, y, nvox % 8 == 0, c % 8 == 0");
     NSLGF_CHECK_ARG(a16(src) && a16(act) && a16(y) && a16(yb), "sur_cast_bf16_ex: tensors must be 16-byte aligned");
     if (nvox == 0) return NSLGF_OK;
-    hipLaunchKernelGGL(k_cast_ex, dim3((unsigned)(ceil_div(nvox, 128) * ceil_div(c, 32))), dim3(256), 0, (hipStream_t)stream,
-                       (const float*)src, (const float*)act, (bf16_t*)y, (bf16_t*)yb, nvox, c, ceil_div(c, 32));
+    const float *x = (const float*)src, *a = (const float*)act;
+    hipStream_t s = (hipStream_t)stream;
+    // Tiles of 64 channels where they divide c, since a tile of 32 leaves half lines of y to the next workgroup (us at
+    // 128^3, 64 channels, with the blocked copy: 219 in tiles of 32, 188 of 64; with act 378 and 295).
+    const int wide = c % 64 == 0 ? 64 : 32, chunks = ceil_div(c, wide);
+    const long long n4 = nvox * c / 4;
+    const dim3 flat((unsigned)ceil_div(n4, 512));
+    if (!yb && a)
+        hipLaunchKernelGGL(k_cast_flat<true>, flat, dim3(256), 0, s, (const float4*)x, (const float4*)a, (uint2*)y, n4);
+    else if (!yb)
+        hipLaunchKernelGGL(k_cast_flat<false>, flat, dim3(256), 0, s, (const float4*)x, nullptr, (uint2*)y, n4);
+    else if (wide == 64)
+        hipLaunchKernelGGL(k_cast_blocked<64>, dim3((unsigned)(ceil_div(nvox, 64) * chunks)), dim3(256), 0, s, x, a,
+                           (bf16_t*)y, (bf16_t*)yb, nvox, c, chunks);
+    else
+        hipLaunchKernelGGL(k_cast_blocked<32>, dim3((unsigned)(ceil_div(nvox, 128) * chunks)), dim3(256), 0, s, x, a,
+                           (bf16_t*)y, (bf16_t*)yb, nvox, c, chunks);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
