@@ -12,7 +12,9 @@
 // ([voxel / 8][channel][8]: a lane's 8 voxels of one channel are one 16-byte word) and gives each wave
 // the three taps of one (dz, dy) pair, over rows staged in an LDS ring.  It reduces over voxels in fixed
 // chunks followed by a fixed-order two-level sum, so every result is deterministic.
+#include <algorithm>
 #include <cmath>
+#include <utility>
 
 #include "../../include/nslgf_surrogate.h"
 #include "kernels.h"
@@ -133,26 +135,29 @@ __global__ void __launch_bounds__(576, MT == 1 ? 7 : 5) k_conv_split(const bf16_
 // two workgroups a CU and took 277).  Rows along y served three dy taps before, which tied the block to 32 voxels
 // along x: widths that 32 does not divide went through the gathering kernel (112^3, 32 -> 32: 328 us, now 123;
 // 56^3, 32 -> 64: 81 and 153 for the data gradient, now 39 and 50; 80^3: 121, now 47).
-constexpr int kLdsZ = 4;  // z planes of a workgroup
-template <int TX> struct LdsBlk {
-    static constexpr int TY = 32 / TX, BY = 4 * TY, HX = TX + 2, HY = BY + 2, HZ = kLdsZ + 2;
+// The form Z = 2 owns TX x (8 TY) x 2 voxels: a wave takes two tiles of y in each of 2 planes, as many matrix
+// operations in all.
+template <int TX, int Z> struct LdsBlk {
+    static constexpr int NY = 4 / Z, TY = 32 / TX, BY = 4 * TY * NY, HX = TX + 2, HY = BY + 2, HZ = Z + 2;
     static constexpr int HALO = HX * HY * HZ, PLANE = (HALO + 7) / 8 * 8 + 4;  // (halves 64 bytes apart in the banks)
 };
-template <bool RELU, int SIGN, int TX>
+template <bool RELU, int SIGN, int TX, int Z>
 __global__ void __launch_bounds__(256) k_conv_lds(const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wn,
                                                   float* __restrict__ Y, int D, int H, int W, int K, int N) {
-    using B = LdsBlk<TX>;
+    using B = LdsBlk<TX, Z>;
     __shared__ uint4 halo[2 * B::PLANE];
     const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
     const int m = lane % 32, half = lane / 32;
     const int xt = (W + TX - 1) / TX;
     const int x0 = (blockIdx.x % xt) * TX, nb = (blockIdx.x / xt) * 32;
-    const int y0 = blockIdx.y * B::BY, z0 = blockIdx.z * kLdsZ;
-    f32x16 acc[kLdsZ];
+    const int y0 = blockIdx.y * B::BY, z0 = blockIdx.z * Z;
+    f32x16 acc[B::NY][Z];
 #pragma unroll
-    for (int r = 0; r < kLdsZ; ++r)
+    for (int t = 0; t < B::NY; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
+        for (int r = 0; r < Z; ++r)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[t][r][i] = 0.f;
     // this thread's halo elements (the same in every slice): offsets from the block's first voxel, in
     // BF16 elements (the host keeps 6 H W K below 2^31), and whether each lies inside the volume
     constexpr int kPer = (B::HALO * 2 + 255) / 256, kFirst = kPer / 2;
@@ -206,57 +211,70 @@ __global__ void __launch_bounds__(256) k_conv_lds(const bf16_t* __restrict__ X, 
             for (int dx = 0; dx < 3; ++dx) {
                 const int nx = 3 * dy + dx + 2;
                 load_b(nx < 9 ? kc : kn, nx < 9 ? nx : nx - 9, b[(dx + 2) % 3]);
-                bf16x8 a[kLdsZ + 2];
+                bf16x8 a[B::NY][Z + 2];
 #pragma unroll
-                for (int j = 0; j < kLdsZ + 2; ++j)
-                    a[j] = __builtin_bit_cast(bf16x8, hp[j * B::HX * B::HY + SIGN * (dx - 1)]);
+                for (int t = 0; t < B::NY; ++t)
+#pragma unroll
+                    for (int j = 0; j < Z + 2; ++j)
+                        a[t][j] = __builtin_bit_cast(bf16x8, hp[(j * B::HY + t * 4 * B::TY) * B::HX + SIGN * (dx - 1)]);
 #pragma unroll
                 for (int dz = 1; dz >= -1; --dz)
 #pragma unroll
-                    for (int r = 0; r < kLdsZ; ++r)
-                        acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[r + SIGN * dz + 1], b[dx][dz + 1], acc[r], 0, 0, 0);
+                    for (int t = 0; t < B::NY; ++t)
+#pragma unroll
+                        for (int r = 0; r < Z; ++r)
+                            acc[t][r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t][r + SIGN * dz + 1], b[dx][dz + 1],
+                                                                                acc[t][r], 0, 0, 0);
             }
         }
     }
 #pragma unroll
-    for (int r = 0; r < kLdsZ; ++r) {
+    for (int r = 0; r < Z; ++r) {
         if (z0 + r >= D) break;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = split_row(i, half);
-            const int xx = x0 + row % TX, yy = y0 + wave * B::TY + row / TX;
-            float val = acc[r][i];
-            if (RELU) val = fmaxf(val, 0.f);
-            if (xx < W && yy < H) Y[(((long long)(z0 + r) * H + yy) * W + xx) * N + nb + m] = val;
-        }
+        for (int t = 0; t < B::NY; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int row = split_row(i, half);
+                const int xx = x0 + row % TX, yy = y0 + (4 * t + wave) * B::TY + row / TX;
+                float val = acc[t][r][i];
+                if (RELU) val = fmaxf(val, 0.f);
+                if (xx < W && yy < H) Y[(((long long)(z0 + r) * H + yy) * W + xx) * N + nb + m] = val;
+            }
     }
 }
 
-template <int TX> static long long lds_blocks(int D, int H, int W) {
-    return (long long)ceil_div(W, TX) * ceil_div(H, LdsBlk<TX>::BY) * ceil_div(D, kLdsZ);
+template <int TX, int Z> static long long lds_blocks(int D, int H, int W) {
+    return (long long)ceil_div(W, TX) * ceil_div(H, LdsBlk<TX, Z>::BY) * ceil_div(D, Z);
 }
-template <bool RELU, int SIGN, int TX>
+template <bool RELU, int SIGN, int TX, int Z>
 static void launch_conv_lds(const bf16_t* x, const bf16_t* w, float* y, int D, int H, int W, int K, int N,
                             hipStream_t s) {
     // one output tile per workgroup: more workgroups on the small volumes, and more tiles would hold
     // 64 more accumulator registers per lane and tile
-    const dim3 grid((unsigned)(ceil_div(W, TX) * (N / 32)), ceil_div(H, LdsBlk<TX>::BY), ceil_div(D, kLdsZ));
-    hipLaunchKernelGGL((k_conv_lds<RELU, SIGN, TX>), grid, dim3(256), 0, s, x, w, y, D, H, W, K, N);
+    const dim3 grid((unsigned)(ceil_div(W, TX) * (N / 32)), ceil_div(H, LdsBlk<TX, Z>::BY), ceil_div(D, Z));
+    hipLaunchKernelGGL((k_conv_lds<RELU, SIGN, TX, Z>), grid, dim3(256), 0, s, x, w, y, D, H, W, K, N);
 }
 // The block shape with the fewest blocks (the least work beyond the volume's edges; 16 wide in a tie: 128^3,
 // 32 -> 32: 194 us forward and 185 for the data gradient, 32 wide 193 and 195, 8 wide 195 and 198).  The split
 // kernel below 48 workgroups, where most CUs would idle over 4 us a slice (16^3, 96 -> 128 with 32 workgroups:
 // 24 us against 15; 24^3, 64 -> 96 with 108: 24 against 39), and where a block's offsets pass 32 bits or the
-// grid its limits.
+// grid its limits.  Two planes a workgroup where that saves 15 % of the blocks, which is on few planes that 4 does
+// not divide (us with four and two: 2 x 128 x 128, 256 -> 256: 239 and 141, 96 -> 128: 46 and 34; 6 x 128 x 128,
+// 256 -> 256: 485 and 404; where it saves less, 34 x 64 x 64, 32 -> 64 data gradient: 39 and 45).
 template <bool RELU, int SIGN>
 static void launch_conv(const bf16_t* x, const bf16_t* w, float* y, int D, int H, int W, int K, int N, hipStream_t s) {
     const long long nvox = (long long)D * H * W;
-    const long long b8 = lds_blocks<8>(D, H, W), b16 = lds_blocks<16>(D, H, W), b32 = lds_blocks<32>(D, H, W);
-    long long b = b16;
-    int tx = 16;
-    if (b32 < b) b = b32, tx = 32;
-    if (b8 < b) b = b8, tx = 8;
-    if (b * (N / 32) < 48 || 6LL * H * W * K >= (1LL << 31) || D / kLdsZ >= 65535 || H / 4 >= 65535) {
+    using Form = std::pair<long long, void (*)(const bf16_t*, const bf16_t*, float*, int, int, int, int, int, hipStream_t)>;
+    const auto fewest = [](const Form& p, const Form& q) { return p.first < q.first; };
+    Form f = std::min({Form{lds_blocks<16, 4>(D, H, W), launch_conv_lds<RELU, SIGN, 16, 4>},
+                       Form{lds_blocks<32, 4>(D, H, W), launch_conv_lds<RELU, SIGN, 32, 4>},
+                       Form{lds_blocks<8, 4>(D, H, W), launch_conv_lds<RELU, SIGN, 8, 4>}}, fewest);
+    const Form flat = std::min({Form{lds_blocks<16, 2>(D, H, W), launch_conv_lds<RELU, SIGN, 16, 2>},
+                                Form{lds_blocks<32, 2>(D, H, W), launch_conv_lds<RELU, SIGN, 32, 2>},
+                                Form{lds_blocks<8, 2>(D, H, W), launch_conv_lds<RELU, SIGN, 8, 2>}}, fewest);
+    if (20 * flat.first <= 17 * f.first) f = flat;
+    if (f.first * (N / 32) < 48 || 6LL * H * W * K >= (1LL << 31) || D / 2 >= 65535 || H / 4 >= 65535) {
         const long long nt = N / 32, tiles = nvox / 32 * nt, pairs = (nvox + 63) / 64 * nt, most = 1 << 22;
         if (tiles < 256)
             hipLaunchKernelGGL((k_conv_split<RELU, SIGN, 1>), dim3((unsigned)tiles), dim3(576), 0, s, x, w, y, D, H, W,
@@ -266,9 +284,7 @@ static void launch_conv(const bf16_t* x, const bf16_t* w, float* y, int D, int H
                                0, s, x, w, y, D, H, W, K, N, pairs);
         return;
     }
-    if (tx == 8) launch_conv_lds<RELU, SIGN, 8>(x, w, y, D, H, W, K, N, s);
-    else if (tx == 16) launch_conv_lds<RELU, SIGN, 16>(x, w, y, D, H, W, K, N, s);
-    else launch_conv_lds<RELU, SIGN, 32>(x, w, y, D, H, W, K, N, s);
+    f.second(x, w, y, D, H, W, K, N, s);
 }
 
 // Channels-last [nvox][C] -> blocked [nvox / 8][C][8] (BF16): within each group of 8 consecutive voxels the
