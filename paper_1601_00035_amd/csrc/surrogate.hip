@@ -427,6 +427,9 @@ __global__ void __launch_bounds__(256) k_cast_blocked(const float* __restrict__ 
 // rows of S groups and one on each side, zero outside the volume) beside two buffers of dY; the rows of the
 // next step are loaded into registers while the current ones multiply.  A half-wave walks SH groups of a
 // row, so that the voxel before and after a group (dx = -1 and +1) come from groups that it holds.
+// PAIR: rows of one group (W <= 8); the half-waves take two neighbouring rows instead of two halves of one, of which
+// the second would be empty, and a step is 8 rows (256 -> 256, 64 x 8 x 8: 91 us without, now 65; 32 x 32 x 8: 129, now
+// 83; 96 -> 128 at 8^3: 21.4, now 20.5).
 // PAD: rows of W voxels, W % 8 != 0, filled up with zeros; the one product that would pair such a filler with a
 // voxel of the volume is masked, as are the groups that a half-wave lacks (an infinity there must not count).
 // One workgroup a CU (its LDS, and waves of 140 to 168 registers, of which 4, padded 1, spill at eight groups a
@@ -442,15 +445,19 @@ struct WgradPlan {
     int R, yb, NZ, zb;        // rows and planes of a chunk, and chunks along y and z
     int parts;                // partial sums of a chunk
     int chunks() const { return segs * yb * zb; }
-    size_t lds() const { return (size_t)(3 * (2 * RS + 2) * (2 * SH + 2) + 2 * RS * 2 * SH) * 512; }
+    bool pair() const { return nx == 1; }
+    size_t lds() const {
+        const int sp = pair() ? 1 : 2 * SH;
+        return (size_t)(3 * (2 * RS + 2) * (sp + 2) + 2 * RS * sp) * 512;
+    }
 };
-template <int SH, int RS, bool PAD>
+template <int SH, int RS, bool PAD, bool PAIR>
 __global__ void __launch_bounds__(kWgThreads)
 k_conv_wgrad_ring(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb, float* __restrict__ P, int D, int H, int W,
                   int cin, int cout, WgradPlan pl, int nblocks) {
     extern __shared__ uint4 wg_lds[];
     constexpr int NR = 2 * RS + 2;
-    constexpr int SP = 2 * SH, S2 = SP + 2;  // groups of the two halves, and with their neighbours
+    constexpr int SP = PAIR ? 1 : 2 * SH, S2 = SP + 2;  // groups of a row, and with their neighbours
     constexpr int NX = (3 * RS * S2 * 32 + kWgThreads - 1) / kWgThreads;  // 16-byte words of X of a thread and step
     // consecutive chunks, which share planes of X, on one XCD
     const int bid = (int)(blockIdx.x % 8) * ((int)gridDim.x / 8) + (int)blockIdx.x / 8;
@@ -553,9 +560,10 @@ k_conv_wgrad_ring(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb,
             const bool more = y + RS < y1;
             if (more) load_step(z, y + RS, w);
 #pragma unroll 1
-            for (int rr = 0; rr < RS && y + rr < y1 && g < 9; ++rr) {
-                const uint4* xp = xr + (((dz + 1) * NR + (y + rr + dy + 1) % NR) * S2 + half * SH) * 32 + m;
-                const uint4* ap = yr + ((buf * RS + rr) * SP + half * SH) * 32 + m;
+            for (int rr = 0; rr < RS && y + rr < y1 && g < 9; rr += PAIR ? 2 : 1) {
+                const int row = PAIR ? rr + half : rr, group = PAIR ? 0 : half * SH;  // of this half-wave
+                const uint4* xp = xr + (((dz + 1) * NR + (y + row + dy + 1) % NR) * S2 + group) * 32 + m;
+                const uint4* ap = yr + ((buf * RS + row) * SP + group) * 32 + m;
                 unsigned pv = xp[0].w;
                 uint4 q[SH + 1], av[SH];  // this half-wave's groups and the first words of the one after
 #pragma unroll
@@ -568,7 +576,7 @@ k_conv_wgrad_ring(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb,
                 for (int j = 0; j < SH; ++j) {
                     uint4 c = q[j];
                     unsigned nv = q[j + 1].x;
-                    if (!full && half * SH + j >= live) {  // (no group here: both operands zero)
+                    if (PAIR ? y + row >= y1 : !full && group + j >= live) {  // (no group here: both operands zero)
                         c = make_uint4(0, 0, 0, 0);
                         av[j] = c;
                         pv = 0;
@@ -584,7 +592,7 @@ k_conv_wgrad_ring(const bf16_t* __restrict__ dYb, const bf16_t* __restrict__ Xb,
                     bq.z = (c.z >> 16) | (c.w << 16);
                     bq.w = (c.w >> 16) | (nv << 16);
                     pv = c.w;
-                    if (PAD && gx0 + half * SH + j == nx - 1) {  // (the row's last voxel has no neighbour x + 1)
+                    if (PAD && gx0 + group + j == nx - 1) {  // (the row's last voxel has no neighbour x + 1)
                         const unsigned keep = W % 2 ? 0xffffu : 0xffff0000u;
                         if (W % 8 / 2 == 0) bm.x &= keep;
                         if (W % 8 / 2 == 1) bm.y &= keep;
@@ -954,7 +962,7 @@ static WgradPlan wgrad_plan(int D, int H, int W, int cin, int cout) {
     p.S = ceil_div(p.nx, p.segs);
     p.segs = ceil_div(p.nx, p.S);
     p.SH = (p.S + 1) / 2;
-    p.RS = p.SH >= 3 ? 2 : 4;
+    p.RS = p.pair() ? 8 : p.SH >= 3 ? 2 : 4;
     const long long per = (long long)(cout / 32) * ceil_div(cin, 32) * p.segs;
     double best = 0;
     p.R = H;
@@ -986,11 +994,11 @@ static WgradPlan wgrad_plan(int D, int H, int W, int cin, int cout) {
 static bool wgrad_blocked_ok(int W, long long nvox) { return W % 8 == 0 && nvox % 16 == 0; }
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-template <int SH, int RS, bool PAD>
+template <int SH, int RS, bool PAD, bool PAIR>
 static int launch_wgrad_ring(const WgradPlan& p, const bf16_t* dyc, const bf16_t* xc, float* part, int D, int H, int W,
                              int cin, int cout, hipStream_t s) {
     const int blocks = p.chunks() * (cout / 32) * ceil_div(cin, 32);
-    hipLaunchKernelGGL((k_conv_wgrad_ring<SH, RS, PAD>), dim3((unsigned)ceil_div(blocks, 8) * 8), dim3(kWgThreads), p.lds(), s,
+    hipLaunchKernelGGL((k_conv_wgrad_ring<SH, RS, PAD, PAIR>), dim3((unsigned)ceil_div(blocks, 8) * 8), dim3(kWgThreads), p.lds(), s,
                        dyc, xc, part, D, H, W, cin, cout, p, blocks);
     return NSLGF_OK;
 }
@@ -1073,10 +1081,11 @@ static int wgrad_from_blocked(const bf16_t* dyc, const bf16_t* xc, float* dw, ch
     const int nch = p.chunks() * p.parts;
     float* part = (float*)work;
     const bool pad = W % 8 != 0;
-#define WGRAD_RING(SH, RS)                                                                          \
-    (pad ? launch_wgrad_ring<SH, RS, true>(p, dyc, xc, part, D, H, W, cin, cout, s)                 \
-         : launch_wgrad_ring<SH, RS, false>(p, dyc, xc, part, D, H, W, cin, cout, s))
-    NSLGF_TRY(p.SH == 4 ? WGRAD_RING(4, 2) : p.SH == 3 ? WGRAD_RING(3, 2) : p.SH == 2 ? WGRAD_RING(2, 4) : WGRAD_RING(1, 4));
+#define WGRAD_RING(SH, RS, PAIR)                                                                    \
+    (pad ? launch_wgrad_ring<SH, RS, true, PAIR>(p, dyc, xc, part, D, H, W, cin, cout, s)           \
+         : launch_wgrad_ring<SH, RS, false, PAIR>(p, dyc, xc, part, D, H, W, cin, cout, s))
+    NSLGF_TRY(p.pair() ? WGRAD_RING(1, 8, true) : p.SH == 4 ? WGRAD_RING(4, 2, false) : p.SH == 3 ? WGRAD_RING(3, 2, false)
+              : p.SH == 2 ? WGRAD_RING(2, 4, false) : WGRAD_RING(1, 4, false));
 #undef WGRAD_RING
     if (nch >= 64) {
         // two levels (groups of 32 chunks, then the groups), each in a fixed order
