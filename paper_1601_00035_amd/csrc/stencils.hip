@@ -3,6 +3,7 @@
 // Every input is read with zero extension outside the box and every output is produced on the box
 // only (the mask operators of Sec. 4.1).  Components (2) and (3) of each printed operator follow from
 // component (1) by the cyclic permutation (component, axis): 1 -> 2 -> 3 -> 1 with x -> y -> z -> x.
+#include <algorithm>
 #include <cmath>
 
 #include "kernels.h"
@@ -408,10 +409,12 @@ __global__ void __launch_bounds__(256) k_max_abs(const T* u, int nx, int ny, int
 // values the averages need) and walks up to kDiagZ planes: every edge vorticity is formed once per tile,
 // neighbours in the plane come through LDS and those of the plane below stay in registers.  (One thread per
 // cell that formed its twelve edge values itself took 235 us at 192^3 in FP64, bound by instructions; this
-// one 93.)
+// one 93.)  Small boxes are split along z until 256 workgroups or 4 planes each, as the walk's planes are its
+// time there (a whole call: 48^3 42 us with a thread per cell, 54 in walks of 24 planes, 29 so; 96^3 68, 60, 46).
 constexpr int kDiagX = 32, kDiagY = 16, kDiagZ = 24;
 static dim3 diag_grid(int nx, int ny, int nz) {
-    return dim3(ceil_div(nx, kDiagX - 1), ceil_div(ny, kDiagY - 1), ceil_div(nz, kDiagZ));
+    const int gx = ceil_div(nx, kDiagX - 1), gy = ceil_div(ny, kDiagY - 1);
+    return dim3(gx, gy, std::max(ceil_div(nz, kDiagZ), std::min(ceil_div(nz, 4), ceil_div(256, gx * gy))));
 }
 int diagnostics_blocks(int nx, int ny, int nz) {
     const dim3 g = diag_grid(nx, ny, nz);
