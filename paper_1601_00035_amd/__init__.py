@@ -530,8 +530,8 @@ def batch_info(device: int | None = None) -> tuple:
 
 
 def herk_step_batched(states: list) -> None:
-    """One step of every state: launched pass by pass the first time, captured into a HIP graph the second
-    time and replayed while the batch is unchanged (same boxes, pointers and step parameters)."""
+    """One step of every state: launched pass by pass the first time, captured into a HIP graph if the next call is
+    on it again, and replayed from then on (same boxes, pointers and step parameters)."""
     if not states:
         return
     dev = states[0].u.device

@@ -336,7 +336,8 @@ int launch_copy(const void* in, void* out, size_t bytes, hipStream_t s) {
         return NSLGF_EINVAL;
     }
     const long long n16 = (long long)(bytes / 16);
-    hipLaunchKernelGGL(k_copy, dim3(4096), dim3(256), 0, s, (const uint4*)in, (uint4*)out, n16);
+    hipLaunchKernelGGL(k_copy, dim3((unsigned)std::clamp((n16 + 255) / 256, 1LL, 4096LL)), dim3(256), 0, s,
+                       (const uint4*)in, (uint4*)out, n16);
     NSLGF_LAUNCH_CHECK();
     return NSLGF_OK;
 }
